@@ -90,8 +90,8 @@ typedef struct {
  * 256 bins they are an error (FBDT_E_NAN).  x: device float32 [d][ldx];
  * boundaries: host float32 [d][B-1] (output); xb: device uint8 [d][ldb]
  * (output; only the first n bytes of each row are written).  1 <= d <= 255,
- * 2 <= n_bins <= 256, n >= 1.  The sort runs on the device (one radix sort
- * per batch of features, scratch held by the library); the call
+ * 2 <= n_bins <= 256, n >= 1.  The order statistics are found on the device
+ * by counting the values' digits (scratch held by the library); the call
  * synchronises the stream.
  */
 int fbdt_bin(const float *x, int64_t n, int32_t d, int64_t ldx, int32_t n_bins,

@@ -101,6 +101,7 @@ int device_info(int dev, DeviceInfo *out) {
         HIP_TRY(hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev));
         HIP_TRY(hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
         HIP_TRY(prepare_kernels((size_t)lds));
+        HIP_TRY(prepare_quantiles((size_t)lds));
         // the no-allocation scratch of this device (dev is the current
         // device here: callers pass the id hipGetDevice returned)
         void *sp = nullptr;
@@ -486,7 +487,7 @@ static int encode_with(const float *x, int64_t n, int32_t d, int64_t ldx, int32_
     HIP_TRY(launch_fill_u32(err, 0u, 1, s));
     {
         Timed t(FBDT_K_ENCODE, s, (double)n * d * 5.0);
-        HIP_TRY(launch_encode(x, ldx, n, d, bounds, n_bins, xb, ldb, err, s));
+        HIP_TRY(launch_encode(x, ldx, n, d, bounds, n_bins, xb, ldb, err, nullptr, di.cu_count, s));
         t.done();
     }
     int h_err = 0;
@@ -527,42 +528,34 @@ int fbdt_bin(const float *x, int64_t n, int32_t d, int64_t ldx, int32_t n_bins,
     DeviceInfo di;
     if ((rc = current_device(&dev, &di))) return rc;
     // Exact order statistics on the device: boundary k of feature j is the
-    // value of rank floor(k n / B) of the feature (section 2.2), read off a
-    // radix sort of the feature's values; then every value is encoded.
-    QuantileScratch qs;
-    HIP_TRY(quantile_scratch(n, d, &qs));
+    // value of rank floor(k n / B) of the feature (section 2.2), found by
+    // counting; then every value is encoded, unless a NaN forbids it (the
+    // encode pass sees the flag), and boundaries and flag come back together.
+    const QuantileShape qs = plan_quantiles(n, d, di.cu_count);
     const size_t nb = (size_t)d * (n_bins - 1);
     Arena &a = g_arena[dev];
     std::lock_guard<std::mutex> lk(a.mu);
     Carver cv;
-    uint64_t *keys_a, *keys_b;
-    char *temp;
-    unsigned long long *nan_count;
-    float *bounds;
-    int *err;
-    cv.add(&keys_a, qs.key_elems);
-    cv.add(&keys_b, qs.key_elems);
-    cv.add(&temp, std::max<size_t>(qs.temp_bytes, 1));
-    cv.add(&nan_count, (size_t)d);
-    cv.add(&bounds, nb);
-    cv.add(&err, 1);
+    char *qscratch;
+    float *bounds;   // the boundaries, then the error word
+    cv.add(&qscratch, quantile_scratch_bytes(qs, d));
+    cv.add(&bounds, nb + 1);
     if ((rc = arena_reserve(a, cv.off))) return rc;
     cv.assign(a.ptr);
+    int *err = reinterpret_cast<int *>(bounds + nb);
     HIP_TRY(launch_fill_u32(err, 0u, 1, s));
-    HIP_TRY(launch_quantile_boundaries(x, ldx, n, d, n_bins, qs, keys_a, keys_b, temp, nan_count,
-                                       bounds, err, s));
-    int h_err = 0;
-    if ((rc = read_err(err, s, &h_err))) return rc;
-    if (h_err & kErrNan)
-        return fail(FBDT_E_NAN, "NaN among the feature values needs n_bins <= 255");
+    HIP_TRY(launch_quantile_boundaries(x, ldx, n, d, n_bins, qs, qscratch, bounds, err, s));
     {
         Timed t(FBDT_K_ENCODE, s, (double)n * d * 5.0);
-        HIP_TRY(launch_encode(x, ldx, n, d, bounds, n_bins, xb, ldb, err, s));
+        HIP_TRY(launch_encode(x, ldx, n, d, bounds, n_bins, xb, ldb, err,
+                              n_bins > kMissingCode ? err : nullptr, di.cu_count, s));
         t.done();
     }
-    std::vector<float> host(nb);
-    HIP_TRY(hipMemcpyAsync(host.data(), bounds, nb * sizeof(float), hipMemcpyDeviceToHost, s));
-    if ((rc = read_err(err, s, &h_err))) return rc;
+    std::vector<float> host(nb + 1);
+    HIP_TRY(hipMemcpyAsync(host.data(), bounds, (nb + 1) * sizeof(float), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    int h_err = 0;
+    std::memcpy(&h_err, host.data() + nb, sizeof h_err);
     if (h_err & kErrNan) return fail(FBDT_E_NAN, "NaN among the feature values needs n_bins <= 255");
     std::memcpy(boundaries, host.data(), nb * sizeof(float));
     return FBDT_OK;

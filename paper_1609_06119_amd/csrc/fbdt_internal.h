@@ -27,6 +27,29 @@ enum : int {
 // that node (its terminal node, whose boost weight it takes).
 constexpr int kMissingCode = 255;
 
+// Inclusive prefix sum of a 64-bit value over the 64 lanes of a wavefront
+// with DPP lane moves (no LDS round trip): a Hillis-Steele scan within each
+// row of 16 lanes (row_shr 1, 2, 4, 8), then the last lane of row 0 and 2
+// added to rows 1 and 3 (row_bcast 15) and the last lane of row 1 to rows 2
+// and 3 (row_bcast 31).  Lanes that a move does not reach receive 0.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ unsigned long long dpp_u64(unsigned long long x) {
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)x, CTRL, ROW_MASK, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(x >> 32), CTRL, ROW_MASK, 0xf,
+                                               true);
+    return ((unsigned long long)(uint32_t)hi << 32) | (uint32_t)lo;
+}
+
+__device__ __forceinline__ unsigned long long wave_inclusive_scan_u64(unsigned long long x) {
+    x += dpp_u64<0x111, 0xf>(x);   // row_shr:1
+    x += dpp_u64<0x112, 0xf>(x);   // row_shr:2
+    x += dpp_u64<0x114, 0xf>(x);   // row_shr:4
+    x += dpp_u64<0x118, 0xf>(x);   // row_shr:8
+    x += dpp_u64<0x142, 0xa>(x);   // row_bcast:15 into rows 1, 3
+    x += dpp_u64<0x143, 0xc>(x);   // row_bcast:31 into rows 2, 3
+    return x;
+}
+
 // Launch shape of one histogram pass.
 struct HistShape {
     int features_per_group;   // features whose histograms one workgroup keeps in LDS
@@ -438,26 +461,27 @@ hipError_t launch_apply_float(const ApplyShape &as, const float *x, int64_t ldx,
                               double f0, float *prob, double *score, hipStream_t s);
 
 // Equal-frequency boundaries on the device: for every feature the value of
-// rank floor(k n / B), k = 1 .. B - 1, from a radix sort of the feature's
-// values (batches of features whose keys together stay <= kQuantileBatchKeys).
-constexpr int64_t kQuantileBatchKeys = (int64_t)1 << 27;
-struct QuantileScratch {
-    int batch_features;   // features sorted together
-    size_t key_elems;     // 64-bit keys per buffer (two buffers)
-    size_t temp_bytes;    // sort scratch
+// rank floor(k m / B), k = 1 .. B - 1, among its m non-NaN values, found by
+// counting digits of the values' images (no sort).
+struct QuantileShape {
+    bool small;        // one workgroup per feature does it all
+    int chunks;        // workgroups per feature of a count
+    int64_t per;       // values per workgroup
 };
-int quantile_batch_features(int64_t n, int d);
-hipError_t quantile_scratch(int64_t n, int d, QuantileScratch *qs);
-// x: device float32 [d][ldx]; bounds: device float32 [d][n_bins - 1], over
-// the non-NaN values of each feature; nan_count: device [d] scratch; err
-// receives kErrNan if a value is NaN and n_bins > kMissingCode.
+QuantileShape plan_quantiles(int64_t n, int d, int cu_count);
+size_t quantile_scratch_bytes(const QuantileShape &qs, int d);
+hipError_t prepare_quantiles(size_t max_lds);   // as prepare_kernels
+// x: device float32 [d][ldx]; bounds: device float32 [d][n_bins - 1];
+// scratch: quantile_scratch_bytes, 256-byte aligned; err receives kErrNan if
+// a value is NaN and n_bins > kMissingCode.
 hipError_t launch_quantile_boundaries(const float *x, int64_t ldx, int64_t n, int d, int n_bins,
-                                      const QuantileScratch &qs, uint64_t *keys_a,
-                                      uint64_t *keys_b, void *temp,
-                                      unsigned long long *nan_count, float *bounds, int *err,
-                                      hipStream_t s);
+                                      const QuantileShape &qs, void *scratch, float *bounds,
+                                      int *err, hipStream_t s);
 
+// Codes of the first n values of every row.  skip (or null): nothing is
+// written if *skip holds kErrNan when the pass starts.
 hipError_t launch_encode(const float *x, int64_t ldx, int64_t n, int d, const float *bounds,
-                         int n_bins, uint8_t *xb, int64_t ldb, int *err, hipStream_t s);
+                         int n_bins, uint8_t *xb, int64_t ldb, int *err, const int *skip,
+                         int cu_count, hipStream_t s);
 
 }  // namespace fbdt
