@@ -33,16 +33,19 @@ struct fbdt_model {
         int device;
         uint16_t *cuts;
         double *leaves;
-        int nodes_stride;   // tile stride the node records were made for (0: none)
-        uint32_t *nodes;    // [T][16] node records of shallow forests, or null
+        // [T][16] node records of shallow forests, or null, and the tile stride
+        // they were made for: [1] for launches that split the trees, so that
+        // calls of few and of many events, which may overlap, do not share any
+        int nodes_stride[2];
+        uint32_t *nodes[2];
         uint2 *frec;        // [T][2^D - 1] (feature, threshold) for float apply, or null
         double *gains;      // [T][2^D - 1] separation gains, or null
         // float apply of shallow forests: per-feature threshold table and the
         // node records (threshold ranks) for the tile stride fnodes_stride
         uint32_t *ftab;
         int ftab_words;
-        uint32_t *fnodes;
-        int fnodes_stride;
+        uint32_t *fnodes[2];
+        int fnodes_stride[2];
     };
     std::mutex mu;
     std::vector<DeviceCopy> copies;
@@ -1094,12 +1097,14 @@ int fbdt_model_set_boundaries(fbdt_model *m, const float *boundaries) {
         if (hipSetDevice(c.device) == hipSuccess) {
             if (c.frec) (void)hipFree(c.frec);
             if (c.ftab) (void)hipFree(c.ftab);
-            if (c.fnodes) (void)hipFree(c.fnodes);
+            for (int q = 0; q < 2; ++q) {
+                if (c.fnodes[q]) (void)hipFree(c.fnodes[q]);
+                c.fnodes[q] = nullptr;
+                c.fnodes_stride[q] = 0;
+            }
             c.frec = nullptr;
             c.ftab = nullptr;
-            c.fnodes = nullptr;
             c.ftab_words = 0;
-            c.fnodes_stride = 0;
         }
     if (cur >= 0) (void)hipSetDevice(cur);
     return FBDT_OK;
@@ -1113,11 +1118,13 @@ void fbdt_model_free(fbdt_model *m) {
         if (hipSetDevice(c.device) == hipSuccess) {
             (void)hipFree(c.cuts);
             (void)hipFree(c.leaves);
-            if (c.nodes) (void)hipFree(c.nodes);
             if (c.frec) (void)hipFree(c.frec);
             if (c.gains) (void)hipFree(c.gains);
             if (c.ftab) (void)hipFree(c.ftab);
-            if (c.fnodes) (void)hipFree(c.fnodes);
+            for (int q = 0; q < 2; ++q) {
+                if (c.nodes[q]) (void)hipFree(c.nodes[q]);
+                if (c.fnodes[q]) (void)hipFree(c.fnodes[q]);
+            }
         }
     }
     if (cur >= 0) (void)hipSetDevice(cur);
@@ -1149,7 +1156,8 @@ static int device_copy(fbdt_model *m, int dev, fbdt_model::DeviceCopy **out) {
         }
         std::copy(m->leaf.begin() + t * nleaf, m->leaf.begin() + (t + 1) * nleaf, row);
     }
-    fbdt_model::DeviceCopy c{dev, nullptr, nullptr, 0, nullptr, nullptr, nullptr};
+    fbdt_model::DeviceCopy c{};
+    c.device = dev;
     HIP_TRY(device_alloc(reinterpret_cast<void **>(&c.cuts), packed.size() * sizeof(uint16_t)));
     if (device_alloc(reinterpret_cast<void **>(&c.leaves), values.size() * sizeof(double)) !=
         hipSuccess) {
@@ -1193,24 +1201,24 @@ int fbdt_apply(const fbdt_model *mc, const uint8_t *xb, int64_t n, int32_t d, in
         std::lock_guard<std::mutex> lk(m->mu);
         fbdt_model::DeviceCopy *copy = nullptr;
         if ((rc = device_copy(m, dev, &copy))) return rc;
-        if (as.shallow && copy->nodes_stride != apply_node_stride(as)) {
+        if (as.shallow && copy->nodes_stride[as.split] != apply_node_stride(as)) {
             // node records for this launch's tile stride
             const int xs = apply_node_stride(as);
             std::vector<uint32_t> table((size_t)T * 16, 0u);
             for (size_t t = 0; t < (size_t)T; ++t)
                 for (size_t k = 0; k < nin; ++k) {
                     table[t * 16 + k] = (uint32_t)m->cut_feature[t * nin + k] * (uint32_t)xs;
-                    table[t * 16 + 8 + k] = (256u - m->cut_bin[t * nin + k]) * 0x10001u;
+                    table[t * 16 + 8 + k] = (256u - m->cut_bin[t * nin + k]) * 0x01010101u;
                 }
-            if (!copy->nodes)
-                HIP_TRY(device_alloc(reinterpret_cast<void **>(&copy->nodes),
+            if (!copy->nodes[as.split])
+                HIP_TRY(device_alloc(reinterpret_cast<void **>(&copy->nodes[as.split]),
                                      table.size() * sizeof(uint32_t)));
-            HIP_TRY(hipMemcpy(copy->nodes, table.data(), table.size() * sizeof(uint32_t),
+            HIP_TRY(hipMemcpy(copy->nodes[as.split], table.data(), table.size() * sizeof(uint32_t),
                               hipMemcpyHostToDevice));
-            copy->nodes_stride = xs;
+            copy->nodes_stride[as.split] = xs;
         }
         cuts = copy->cuts;
-        nodes = copy->nodes;
+        nodes = copy->nodes[as.split];
         leaves = copy->leaves;
     }
     Timed tm(FBDT_K_APPLY, s, (double)n * (m->n_features + 4));
@@ -1302,67 +1310,70 @@ int fbdt_apply_float(const fbdt_model *mc, const float *x, int64_t n, int32_t d,
         auto threshold = [&](size_t k) {
             return m->boundaries[(size_t)m->cut_feature[k] * nb + m->cut_bin[k] - 1];
         };
-        std::vector<uint32_t> rank;   // per node: rank of its threshold (shallow)
-        if (shallow && !copy->ftab) {
-            // per feature, the ascending distinct thresholds its cuts test
-            // (equal values, +0 and -0 included, decide alike: one entry)
-            const int d_used = m->n_features;
-            std::vector<std::vector<float>> per(d_used);
+        // per feature, the ascending distinct thresholds its cuts test (equal
+        // values, +0 and -0 included, decide alike: one entry)
+        std::vector<std::vector<float>> per;
+        auto collect = [&]() {
+            if (!per.empty()) return;
+            per.resize(m->n_features);
             for (size_t k = 0; k < (size_t)T * nin; ++k)
                 per[m->cut_feature[k]].push_back(threshold(k));
-            std::vector<uint32_t> table(d_used + 1, 0u);
-            for (int f = 0; f < d_used; ++f) {
-                auto &v = per[f];
+            for (auto &v : per) {
                 std::sort(v.begin(), v.end());
-                v.erase(std::unique(v.begin(), v.end(),
-                                    [](float a, float b) { return a == b; }),
+                v.erase(std::unique(v.begin(), v.end(), [](float a, float b) { return a == b; }),
                         v.end());
-                table[f + 1] = table[f] + (uint32_t)v.size();
             }
-            for (int f = 0; f < d_used; ++f)
-                for (float t : per[f]) {
-                    uint32_t bits;
-                    std::memcpy(&bits, &t, sizeof bits);
-                    table.push_back(bits);
-                }
+        };
+        if (shallow && !copy->ftab) {
+            collect();
+            const size_t d_used = m->n_features;
+            std::vector<uint32_t> table(d_used, 0u);
+            for (size_t f = 0; f < d_used; ++f) {
+                const auto &v = per[f];
+                uint32_t levels = 0;
+                while (((size_t)1 << levels) <= v.size()) ++levels;   // 2^levels > thresholds
+                const size_t at = table.size();
+                table[f] = (uint32_t)at << 8 | levels;
+                table.resize(at + ((size_t)1 << levels), 0x7fc00000u);
+                for (uint32_t l = 0; l < levels; ++l)
+                    for (size_t p = 0; p < (size_t)1 << l; ++p) {
+                        const size_t k = (((2 * p + 1) << levels) >> (l + 1)) - 1;
+                        if (k < v.size()) std::memcpy(&table[at + ((size_t)1 << l) + p], &v[k], 4);
+                    }
+            }
             HIP_TRY(device_alloc(reinterpret_cast<void **>(&copy->ftab),
                                  table.size() * sizeof(uint32_t)));
             HIP_TRY(hipMemcpy(copy->ftab, table.data(), table.size() * sizeof(uint32_t),
                               hipMemcpyHostToDevice));
             copy->ftab_words = (int)table.size();
-            copy->fnodes_stride = 0;
         }
         if (shallow) {
             as = plan_apply_float(n, m->n_features, T, D, false, di.cu_count, di.max_lds,
                                   (int)opt_apply_threads.load(),
                                   (size_t)copy->ftab_words * sizeof(uint32_t));
-            if (copy->fnodes_stride != apply_node_stride(as)) {
+            if (copy->fnodes_stride[as.split] != apply_node_stride(as)) {
                 // node records for this launch's tile stride, with threshold ranks
-                std::vector<uint32_t> ttab((size_t)copy->ftab_words);
-                HIP_TRY(hipMemcpy(ttab.data(), copy->ftab, ttab.size() * sizeof(uint32_t),
-                                  hipMemcpyDeviceToHost));
+                collect();
                 const int xs = apply_node_stride(as);
                 std::vector<uint32_t> table((size_t)T * 16, 0u);
-                const uint32_t *off = ttab.data();
-                const float *thr = reinterpret_cast<const float *>(ttab.data() + m->n_features + 1);
                 for (size_t t = 0; t < (size_t)T; ++t)
                     for (size_t k = 0; k < nin; ++k) {
                         const size_t q = t * nin + k;
                         const uint32_t f = m->cut_feature[q];
-                        const float v = threshold(q);
-                        const float *lo = thr + off[f], *hi = thr + off[f + 1];
-                        const uint32_t r = (uint32_t)(std::lower_bound(lo, hi, v) - lo) + 1u;
+                        const auto &v = per[f];
+                        const uint32_t r = (uint32_t)(std::lower_bound(v.begin(), v.end(),
+                                                                       threshold(q)) - v.begin()) + 1u;
                         table[t * 16 + k] = f * (uint32_t)xs;
-                        table[t * 16 + 8 + k] = (256u - r) * 0x10001u;
+                        table[t * 16 + 8 + k] = (256u - r) * 0x01010101u;
                     }
-                if (!copy->fnodes)
-                    HIP_TRY(device_alloc(reinterpret_cast<void **>(&copy->fnodes),
+                if (!copy->fnodes[as.split])
+                    HIP_TRY(device_alloc(reinterpret_cast<void **>(&copy->fnodes[as.split]),
                                          table.size() * sizeof(uint32_t)));
-                HIP_TRY(hipMemcpy(copy->fnodes, table.data(), table.size() * sizeof(uint32_t),
+                HIP_TRY(hipMemcpy(copy->fnodes[as.split], table.data(), table.size() * sizeof(uint32_t),
                                   hipMemcpyHostToDevice));
-                copy->fnodes_stride = xs;
+                copy->fnodes_stride[as.split] = xs;
             }
-            fnodes = copy->fnodes;
+            fnodes = copy->fnodes[as.split];
             ftab = copy->ftab;
             ftab_words = copy->ftab_words;
         } else {

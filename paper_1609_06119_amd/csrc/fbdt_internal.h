@@ -415,21 +415,29 @@ hipError_t launch_hist_list(const ListShape &ls, int lmode, const uint2 *list,
 // Forest traversal.  cuts: [T][2^D-1] packed (feature | bin << 8), for the
 // general kernel; nodes: [T][16] for depth <= kApplyShallowDepth, for heap
 // node k + 1 word k = feature * apply_node_stride (the LDS row offset in the
-// launch's code tile) and word 8 + k = (256 - bin) * 0x10001.
+// launch's code tile) and word 8 + k = (256 - bin) * 0x01010101.
 constexpr int kApplyShallowDepth = 3;
+// Rounds of one workgroup per CU up to which the shallow traversal shares the
+// trees of 256 events among a workgroup's wavefronts: a round takes 14 us for
+// 400 trees of depth 3 over 40 features, a round of the bulk kernel 84 to 100
+// us (of 2,048 or 3,072 events per CU).
+constexpr int kSplitRounds = 6;
 struct ApplyShape {
     bool shallow;          // depth <= kApplyShallowDepth: apply_shallow_kernel
+    bool split;            // apply_split_kernel instead
     bool missing;          // missing values: boost weights of every node per tree (heap
                            // order) and the missing code stops an event at its node
     int threads;
     int blocks;
     int trees_per_chunk;   // trees whose leaf values (and cuts) are staged in LDS at once
     int d_used;
+    int per_cu;            // workgroups per CU (shallow)
+    int node_stride;       // bytes between the features' rows in the code tile (shallow)
     size_t lds_bytes;
 };
 ApplyShape plan_apply(int64_t n, int d_used, int n_trees, int depth, bool missing,
-                      int cu_count, size_t max_lds, int threads);
-inline int apply_node_stride(const ApplyShape &as) { return 2 * as.threads + 8; }
+                      int cu_count, size_t max_lds, int threads, size_t extra_lds = 0);
+inline int apply_node_stride(const ApplyShape &as) { return as.node_stride; }
 hipError_t launch_apply(const ApplyShape &as, const uint8_t *xb, int64_t ldb, int64_t n,
                         const uint16_t *cuts, const uint32_t *nodes, const double *leaves,
                         int n_trees, int depth, double f0, float *prob, double *score,
@@ -447,10 +455,12 @@ hipError_t launch_importance(const ApplyShape &as, const uint8_t *xb, int64_t ld
 // Traversal of float32 events [d][ldx] with value thresholds.  Forests of
 // depth <= kApplyShallowDepth without missing values (as.shallow) take the
 // binned shallow traversal with its code tile staged from the values:
-// ftab = [d_used + 1] offsets, then per feature the ascending distinct
-// thresholds its cuts test (float bits), ftab_words words in all (table_bytes
+// ftab = [d_used] words offset << 8 | levels, then per feature, from its
+// offset, 2^levels words: the ascending distinct thresholds its cuts test
+// (float bits) level by level (entry 2^l + p decides bit l of the codes that
+// start with p; NaN where there is none), ftab_words words in all (table_bytes
 // of LDS); fnodes = node records as for the binned traversal (stride
-// apply_node_stride(as)) with word 8 + k = (256 - c') * 0x10001, c' the rank
+// apply_node_stride(as)) with word 8 + k = (256 - c') * 0x01010101, c' the rank
 // (from 1) of the node's threshold among its feature's.  Other forests walk
 // rec: [T][2^D-1] (feature, float bits of the threshold) per heap node.
 ApplyShape plan_apply_float(int64_t n, int d_used, int n_trees, int depth, bool missing,

@@ -26,6 +26,8 @@ namespace fbdt {
 namespace {
 
 constexpr int kWave = 64;
+// four consecutive floats read or written at the alignment of one
+typedef float float4_unaligned __attribute__((ext_vector_type(4), aligned(4)));
 constexpr int kHistE = 8;      // events per thread and step of the histogram pass
 
 // Workgroup barrier that orders LDS only: this wavefront's LDS operations
@@ -2362,54 +2364,188 @@ __global__ __launch_bounds__(1024) void apply_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// Forest traversal for depth <= 3 (the apply workload's forests).  Every
-// thread scores two adjacent events.  The 2^D - 1 cuts of a tree are uniform
-// across the workgroup, so they come as scalar loads of a per-tree record of
-// 16 words: for heap node k + 1, word k = the LDS offset of its feature's row
-// in the code tile (feature * XS) and word 8 + k = (256 - bin) * 0x10001.  All
-// cuts' codes of both events are read up front (one 16-bit LDS read per cut,
-// no chain from one level to the next); v_perm puts the two codes in the low
-// bytes of the two 16-bit halves, and adding word 8 + k sets bit 8 (first
-// event) and bit 24 (second event) exactly when code >= bin (right child).
-// The path is then bitfield selects on those words for both events at once,
-// and each reached leaf's value is one LDS read, added to F in tree order.
-// Leaf values of tpc trees at a time are staged in LDS (all of them when they
-// fit), the codes of a tile of 2 * blockDim events per feature (row stride XS
-// = 2 * blockDim + 8).
-constexpr int kApplyBatch = 4;
+// Forest traversal for depth <= 3.  Every thread scores four adjacent events,
+// one per byte of a word.  The 2^D - 1 cuts of a tree are uniform across the
+// workgroup, so they come as scalar loads of a per-tree record of 16 words:
+// for heap node k + 1, word k = the LDS offset of its feature's row in the
+// code tile (feature * XS) and word 8 + k = 256 - bin in every byte.  All
+// cuts' codes are read up front (one 32-bit LDS read per cut, no chain from
+// one level to the next); v_lerp_u8, (code + (256 - bin)) >> 1 in every
+// byte, leaves the carry of the byte's sum, code >= bin (right child), in
+// the byte's top bit.  The path is then bitfield selects on those words for
+// four events at once, and each reached leaf's value is one LDS read, added
+// to F in tree order.  Leaf values of tpc trees at a time are staged in LDS
+// (all of them when they fit), the codes of a tile of 4 * blockDim events
+// per feature (row stride XS = 4 * blockDim).
+// About 8 vector instructions per event and tree: bound by their issue and
+// by the LDS (7 words of codes and 4 leaf values per four events).  Two events
+// a thread in 16-bit fields (a byte permute and an add per node, 18.5
+// instructions) took 11.9 ms for 50M events of 40 features and 400 trees of
+// depth 3; now 6.6 ms (81%
+// of the vector issue rate, and no bank conflicts).
+constexpr int kApplyBatch = 2;
 
-// Leaf indices of the two events in a tree of depth D <= 3: the first in
-// bits 0..2, the second in bits 16..18.
-template <int D>
-__device__ __forceinline__ uint32_t shallow_leaf2(const uint8_t *xpair, const uint32_t *off,
-                                                  const uint32_t *add) {
-    constexpr int NIN = (1 << D) - 1;
-    uint32_t w[NIN];
-#pragma unroll
-    for (int k = 0; k < NIN; ++k) {
-        const uint32_t p = *reinterpret_cast<const uint16_t *>(xpair + off[k]);
-        w[k] = __builtin_amdgcn_perm(p, p, 0x0c010c00u) + add[k];
-    }
-    constexpr uint32_t kBits = 0x01000100u;   // the decision bits (8 and 24)
-    const uint32_t r1 = w[0];
-    if (D == 1) return (r1 & kBits) >> 8;
-    const uint32_t r2 = (r1 & w[2]) | (~r1 & w[1]);   // child of the root reached
-    if (D == 2) return ((r1 & kBits) >> 7) | ((r2 & kBits) >> 8);
-    const uint32_t t0 = (r2 & w[4]) | (~r2 & w[3]);
-    const uint32_t t1 = (r2 & w[6]) | (~r2 & w[5]);
-    const uint32_t r3 = (r1 & t1) | (~r1 & t0);
-    return ((r1 & kBits) >> 6) | ((r2 & kBits) >> 7) | ((r3 & kBits) >> 8);
+// Selects, bit by bit, a where m is set and b where it is not.
+__device__ __forceinline__ uint32_t bit_select(uint32_t m, uint32_t a, uint32_t b) {
+    return (m & a) | (~m & b);
 }
 
-// With FLOATS the tile is staged from float32 values (section 2.2's
-// inverse transform, fused): ftab holds, per feature, the ascending distinct
-// thresholds that the forest's cuts on it test (offsets [d_used + 1], then
-// the thresholds' float bits), and a value's code is the number of those
-// thresholds at or below it, found by a binary search in LDS; the node
-// records then carry, instead of the bin c, the rank c' of the node's
-// threshold among its feature's (code >= c' exactly when x >= threshold).
-// NaN compares false with every threshold: code 0, the left branch of every
-// cut, as the threshold test gives.
+// The node records of the trees t0 .. t0 + U - 1, uniform loads.
+typedef uint32_t uint8v __attribute__((ext_vector_type(8)));
+template <int U>
+struct NodeBatch {
+    uint8v off[U], add[U];
+    __device__ __forceinline__ void load(const uint32_t *nodes, int t0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint8v *r = reinterpret_cast<const uint8v *>(nodes + (size_t)(t0 + u) * 16);
+            off[u] = r[0];
+            add[u] = r[1];
+        }
+    }
+};
+
+// Leaves reached by the four events in U trees of depth D <= 3: 8 * leaf in
+// each byte.
+template <int D, int U>
+__device__ __forceinline__ void shallow_leaf4(const uint8_t *xquad, const NodeBatch<U> &nb,
+                                              uint32_t (&m)[U]) {
+    constexpr int NIN = (1 << D) - 1;
+    uint32_t w[U][NIN];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int k = 0; k < NIN; ++k)
+            w[u][k] = *reinterpret_cast<const uint32_t *>(xquad + nb.off[u][k]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+#pragma unroll
+        for (int k = 0; k < NIN; ++k)
+            w[u][k] = __builtin_amdgcn_lerp(w[u][k], nb.add[u][k], 0u);
+        // the decisions in the bytes' top bits
+        const uint32_t r1 = w[u][0];
+        if (D == 1) {
+            m[u] = (r1 >> 4) & 0x08080808u;
+        } else {
+            const uint32_t r2 = bit_select(r1, w[u][D > 1 ? 2 : 0], w[u][D > 1 ? 1 : 0]);
+            uint32_t p = r2 >> 1;
+            p = bit_select(0x80808080u, r1, p);
+            if (D == 2) {
+                m[u] = (p >> 3) & 0x18181818u;
+            } else {
+                const uint32_t t0 = bit_select(r2, w[u][NIN > 4 ? 4 : 0], w[u][NIN > 3 ? 3 : 0]);
+                const uint32_t t1 = bit_select(r2, w[u][NIN > 6 ? 6 : 0], w[u][NIN > 5 ? 5 : 0]);
+                const uint32_t r3 = bit_select(r1, t1, t0);
+                m[u] = (bit_select(0xc0c0c0c0u, p, r3 >> 2) >> 2) & 0x38383838u;
+            }
+        }
+        // (kept as bytes, so that each event's leaf address is one add of a byte)
+        __asm__("" : "+v"(m[u]));
+    }
+}
+
+// Stages a tile of codes in LDS: thread t of nt takes events i0 .. i0 + 3
+// into word t of every feature's row.  Rows of the code matrix are padded to
+// ldb >= round_up(n, 16), so the word is in bounds where i0 < n.
+__device__ __forceinline__ void stage_codes(uint8_t *s_x, int xs, int word,
+                                            const uint8_t *__restrict__ xb, int64_t ldb,
+                                            int64_t n, int64_t i0, int f0, int fstep, int d_used) {
+    if (i0 >= n) return;
+    for (int f = f0; f < d_used; f += 4 * fstep) {
+        uint32_t v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            v[u] = *reinterpret_cast<const uint32_t *>(
+                xb + (int64_t)min(f + u * fstep, d_used - 1) * ldb + i0);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (f + u * fstep < d_used)
+                *reinterpret_cast<uint32_t *>(s_x + (f + u * fstep) * xs + 4 * word) = v[u];
+    }
+}
+
+// Stages a tile of codes from float32 values (section 2.2's inverse
+// transform, fused).  s_tab holds, per feature, the thresholds that the
+// forest's cuts on it test: word f = offset << 8 | levels, and from the
+// offset the ascending distinct thresholds level by level (entry 2^l + p
+// decides bit l of the codes that start with p, missing ones are NaN; see
+// encode_kernel).  A value's code is the number of thresholds at or below
+// it.  NaN compares false with every threshold: code 0, the left branch of
+// every cut, as the threshold test gives.
+__device__ __forceinline__ void stage_values(uint8_t *s_x, int xs, int word,
+                                             const uint32_t *s_tab, const float *__restrict__ xf,
+                                             int64_t ldx, int64_t n, int64_t i0, int f0, int fstep,
+                                             int d_used) {
+    if (i0 >= n) return;
+    const bool whole = i0 + 4 <= n;
+    for (int fb = f0; fb < d_used; fb += 4 * fstep) {
+        float v[4][4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const float *src = xf + (int64_t)min(fb + u * fstep, d_used - 1) * ldx + i0;
+            if (whole) {
+                const float4_unaligned q = *reinterpret_cast<const float4_unaligned *>(src);
+                v[u][0] = q.x;
+                v[u][1] = q.y;
+                v[u][2] = q.z;
+                v[u][3] = q.w;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[u][e] = i0 + e < n ? src[e] : 0.0f;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int f = fb + u * fstep;
+            if (f < d_used) {
+                const uint32_t head = s_tab[f];
+                const float *thr = reinterpret_cast<const float *>(s_tab + (head >> 8));
+                const int levels = (int)(head & 0xffu);
+                uint32_t c[4] = {0u, 0u, 0u, 0u};
+                for (int l = 0; l < levels; ++l)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        c[e] = 2u * c[e] + (thr[(1 << l) + c[e]] <= v[u][e] ? 1u : 0u);
+                *reinterpret_cast<uint32_t *>(s_x + f * xs + 4 * word) =
+                    c[0] | c[1] << 8 | c[2] << 16 | c[3] << 24;
+            }
+        }
+    }
+}
+
+__device__ __forceinline__ double leaf_at(const double *table, uint32_t m, int e) {
+    return *reinterpret_cast<const double *>(reinterpret_cast<const char *>(table) +
+                                             ((m >> (8 * e)) & 0xffu));
+}
+
+__device__ __forceinline__ void store_scores(const double (&F)[4], int64_t i0, int64_t n,
+                                             float *prob, double *score) {
+    if (i0 >= n) return;
+    float p[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) p[e] = (float)(1.0 / (1.0 + exp(-2.0 * F[e])));
+    if (i0 + 4 <= n) {   // (prob may start at any element)
+        float4_unaligned q;
+        q.x = p[0];
+        q.y = p[1];
+        q.z = p[2];
+        q.w = p[3];
+        *reinterpret_cast<float4_unaligned *>(prob + i0) = q;
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (i0 + e < n) prob[i0 + e] = p[e];
+    }
+    if (score) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (i0 + e < n) score[i0 + e] = F[e];
+    }
+}
+
+// With FLOATS the tile is staged from float32 values and the node records
+// carry, instead of the bin c, the rank c' of the node's threshold among its
+// feature's (code >= c' exactly when x >= threshold).
 template <int D, bool FLOATS>
 __global__ __launch_bounds__(1024) void apply_shallow_kernel(
     const uint8_t *__restrict__ xb, int64_t ldb, const float *__restrict__ xf, int64_t ldx,
@@ -2417,126 +2553,153 @@ __global__ __launch_bounds__(1024) void apply_shallow_kernel(
     const uint32_t *__restrict__ nodes, const double *__restrict__ leaves, int T, int tpc,
     double f0, float *__restrict__ prob, double *__restrict__ score) {
     constexpr int NLEAF = 1 << D;
-    constexpr int NIN = (1 << D) - 1;
     extern __shared__ double smem[];
     double *s_leaf = smem;   // [tpc][NLEAF]
     uint8_t *s_x = reinterpret_cast<uint8_t *>(s_leaf + (size_t)tpc * NLEAF);   // [d_used][XS]
-    const int tile_events = 2 * blockDim.x;
-    const int XS = tile_events + 8;   // the stride the node records were prepared for
-    // FLOATS: thresholds per feature, after the code tile (XS is a multiple of 8)
-    uint32_t *s_tab = reinterpret_cast<uint32_t *>(s_x + (size_t)d_used * XS);
-    const float *s_thr = reinterpret_cast<const float *>(s_tab + d_used + 1);
+    const int XS = 4 * blockDim.x;   // the stride the node records were prepared for
+    uint32_t *s_tab = reinterpret_cast<uint32_t *>(s_x + (size_t)d_used * XS);   // FLOATS
     if (FLOATS) {
         for (int q = threadIdx.x; q < ftab_words; q += blockDim.x) s_tab[q] = ftab[q];
     }
     const int nchunks = (T + tpc - 1) / tpc;
-    const int64_t ntiles = (n + tile_events - 1) / tile_events;
-    const uint8_t *xpair = s_x + 2 * threadIdx.x;
+    const int64_t ntiles = (n + XS - 1) / XS;
+    const uint8_t *xquad = s_x + 4 * threadIdx.x;
     bool staged = false;
     for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const int64_t i0 = tile * tile_events + 2 * threadIdx.x;   // this thread's events
-        __syncthreads();
+        const int64_t i0 = tile * XS + 4 * threadIdx.x;   // this thread's events
+        // (a thread stages and reads its own words of the tile only; the
+        // barrier publishes the threshold table)
         if (FLOATS) {
-            // 8 features' values loaded at a time, then their codes searched
-            for (int fb = 0; fb < d_used; fb += 8) {
-                float va[8], vb[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const float *src = xf + (int64_t)min(fb + u, d_used - 1) * ldx + i0;
-                    va[u] = i0 < n ? src[0] : 0.0f;
-                    vb[u] = i0 + 1 < n ? src[1] : 0.0f;
-                }
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int f = fb + u;
-                    if (f >= d_used) break;
-                    const int lo = (int)s_tab[f], m = (int)s_tab[f + 1] - lo;
-                    int ca = 0, cb = 0;
-                    // count of thresholds <= value (binary lifting over m entries)
-                    for (int step = m > 0 ? 1 << (31 - __clz(m)) : 0; step > 0; step >>= 1) {
-                        const int ta = ca + step, tb = cb + step;
-                        if (ta <= m && s_thr[lo + ta - 1] <= va[u]) ca = ta;
-                        if (tb <= m && s_thr[lo + tb - 1] <= vb[u]) cb = tb;
-                    }
-                    *reinterpret_cast<uint16_t *>(s_x + f * XS + 2 * threadIdx.x) =
-                        (uint16_t)(ca | (cb << 8));
-                }
-            }
+            if (!staged) __syncthreads();
+            stage_values(s_x, XS, threadIdx.x, s_tab, xf, ldx, n, i0, 0, 1, d_used);
         } else {
-            for (int f = 0; f < d_used; ++f) {
-                const uint8_t *src = xb + (int64_t)f * ldb + i0;
-                uint16_t pair = 0;
-                if (i0 + 1 < n)
-                    pair = *reinterpret_cast<const uint16_t *>(src);
-                else if (i0 < n)
-                    pair = src[0];
-                *reinterpret_cast<uint16_t *>(s_x + f * XS + 2 * threadIdx.x) = pair;
-            }
+            stage_codes(s_x, XS, threadIdx.x, xb, ldb, n, i0, 0, 1, d_used);
         }
-        double Fa = f0, Fb = f0;
+        double F[4] = {f0, f0, f0, f0};
         for (int ch = 0; ch < nchunks; ++ch) {
             const int t0 = ch * tpc;
             const int tc = min(tpc, T - t0);
             if (nchunks > 1 || !staged) {
-                __syncthreads();
+                __syncthreads();   // the chunk before is done with the table
                 for (int q = threadIdx.x; q < tc * NLEAF; q += blockDim.x)
                     s_leaf[q] = leaves[(size_t)t0 * NLEAF + q];
                 staged = true;
+                __syncthreads();
             }
-            __syncthreads();
-            // full batches of kApplyBatch trees: every load of the batch (node
-            // records, codes, leaf values) is issued before its results are
-            // used, then the leaf values are added in tree order
+            // full batches of kApplyBatch trees: the next batch's node records
+            // load while the batch is decided, its codes' reads and then its
+            // leaf values' are issued together, and the leaf values are added
+            // in tree order
+            const int whole = tc / kApplyBatch * kApplyBatch;
+            NodeBatch<kApplyBatch> nb;
+            if (whole > 0) nb.load(nodes, t0);
             int t = 0;
-            for (; t + kApplyBatch <= tc; t += kApplyBatch) {
-                uint32_t off[kApplyBatch][NIN], add[kApplyBatch][NIN];
+            for (; t < whole; t += kApplyBatch) {
+                NodeBatch<kApplyBatch> next;
+                next.load(nodes, t0 + min(t + kApplyBatch, whole - kApplyBatch));
+                uint32_t m[kApplyBatch];
+                shallow_leaf4<D, kApplyBatch>(xquad, nb, m);
+                double l[kApplyBatch][4];
 #pragma unroll
-                for (int u = 0; u < kApplyBatch; ++u) {
-                    const uint32_t *nt = nodes + (size_t)(t0 + t + u) * 16;
+                for (int u = 0; u < kApplyBatch; ++u)
 #pragma unroll
-                    for (int k = 0; k < NIN; ++k) {
-                        off[u][k] = nt[k];
-                        add[u][k] = nt[8 + k];
-                    }
-                }
-                uint32_t idx[kApplyBatch];
+                    for (int e = 0; e < 4; ++e) l[u][e] = leaf_at(s_leaf + (t + u) * NLEAF, m[u], e);
 #pragma unroll
-                for (int u = 0; u < kApplyBatch; ++u) idx[u] = shallow_leaf2<D>(xpair, off[u], add[u]);
-                double la[kApplyBatch], lb[kApplyBatch];
+                for (int u = 0; u < kApplyBatch; ++u)
 #pragma unroll
-                for (int u = 0; u < kApplyBatch; ++u) {
-                    const double *lt = s_leaf + (t + u) * NLEAF;
-                    la[u] = lt[idx[u] & 0xffffu];
-                    lb[u] = lt[idx[u] >> 16];
-                }
-#pragma unroll
-                for (int u = 0; u < kApplyBatch; ++u) {
-                    Fa += la[u];
-                    Fb += lb[u];
-                }
+                    for (int e = 0; e < 4; ++e) F[e] += l[u][e];
+                nb = next;
             }
             for (; t < tc; ++t) {
-                const uint32_t *nt = nodes + (size_t)(t0 + t) * 16;
-                uint32_t off[NIN], add[NIN];
+                NodeBatch<1> one;
+                one.load(nodes, t0 + t);
+                uint32_t m[1];
+                shallow_leaf4<D, 1>(xquad, one, m);
 #pragma unroll
-                for (int k = 0; k < NIN; ++k) {
-                    off[k] = nt[k];
-                    add[k] = nt[8 + k];
-                }
-                const uint32_t idx = shallow_leaf2<D>(xpair, off, add);
-                const double *lt = s_leaf + t * NLEAF;
-                Fa += lt[idx & 0xffffu];
-                Fb += lt[idx >> 16];
+                for (int e = 0; e < 4; ++e) F[e] += leaf_at(s_leaf + t * NLEAF, m[0], e);
             }
         }
-        if (i0 < n) {
-            prob[i0] = (float)(1.0 / (1.0 + exp(-2.0 * Fa)));
-            if (score) score[i0] = Fa;
+        store_scores(F, i0, n, prob, score);
+    }
+}
+
+// The same traversal for few events: a workgroup takes kSplitEvents events
+// and its wavefronts share the trees.  Each wavefront finds the leaves that the
+// events reach in its trees (four events per lane, 8 * leaf in the bytes of
+// s_m[tree][lane]); then a thread per event adds the leaf values in tree
+// order.  With one chain of batches per thread the bulk kernel takes the time
+// of all the trees' loads one after another whatever the number of events
+// (400 trees of depth 3: 78 us a call for 1,000 events of 40 features, here
+// 16 us; 260,000 events: 57 us, about 100 us in the bulk kernel).
+constexpr int kSplitEvents = 256;
+constexpr int kSplitThreads = 1024;
+template <int D, bool FLOATS>
+__global__ __launch_bounds__(kSplitThreads) void apply_split_kernel(
+    const uint8_t *__restrict__ xb, int64_t ldb, const float *__restrict__ xf, int64_t ldx,
+    const uint32_t *__restrict__ ftab, int ftab_words, int64_t n, int d_used,
+    const uint32_t *__restrict__ nodes, const double *__restrict__ leaves, int T, int tpc,
+    double f0, float *__restrict__ prob, double *__restrict__ score) {
+    constexpr int NLEAF = 1 << D;
+    constexpr int XS = kSplitEvents;   // the stride the node records were prepared for
+    constexpr int kWaves = kSplitThreads / kWave;
+    extern __shared__ double smem[];
+    double *s_leaf = smem;                                                       // [tpc][NLEAF]
+    uint32_t *s_m = reinterpret_cast<uint32_t *>(s_leaf + (size_t)tpc * NLEAF);  // [tpc][kWave]
+    uint8_t *s_x = reinterpret_cast<uint8_t *>(s_m + (size_t)tpc * kWave);       // [d_used][XS]
+    uint32_t *s_tab = reinterpret_cast<uint32_t *>(s_x + (size_t)d_used * XS);   // FLOATS
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const int64_t base = (int64_t)blockIdx.x * kSplitEvents;
+    if (FLOATS) {
+        for (int q = threadIdx.x; q < ftab_words; q += kSplitThreads) s_tab[q] = ftab[q];
+        __syncthreads();
+        stage_values(s_x, XS, lane, s_tab, xf, ldx, n, base + 4 * lane, wave, kWaves, d_used);
+    } else {
+        stage_codes(s_x, XS, lane, xb, ldb, n, base + 4 * lane, wave, kWaves, d_used);
+    }
+    double F = f0;
+    for (int t0 = 0; t0 < T; t0 += tpc) {
+        const int tc = min(tpc, T - t0);
+        if (t0 > 0) __syncthreads();   // the chunk before is summed
+        for (int q = threadIdx.x; q < tc * NLEAF; q += kSplitThreads)
+            s_leaf[q] = leaves[(size_t)t0 * NLEAF + q];
+        if (t0 == 0) __syncthreads();   // the codes are staged
+        const uint8_t *xquad = s_x + 4 * lane;
+        const int w0 = __builtin_amdgcn_readfirstlane(wave);
+        int t = w0 * kApplyBatch;
+        for (; t + kApplyBatch <= tc; t += kWaves * kApplyBatch) {
+            NodeBatch<kApplyBatch> nb;
+            nb.load(nodes, t0 + t);
+            uint32_t m[kApplyBatch];
+            shallow_leaf4<D, kApplyBatch>(xquad, nb, m);
+#pragma unroll
+            for (int u = 0; u < kApplyBatch; ++u) s_m[(t + u) * kWave + lane] = m[u];
         }
-        if (i0 + 1 < n) {
-            prob[i0 + 1] = (float)(1.0 / (1.0 + exp(-2.0 * Fb)));
-            if (score) score[i0 + 1] = Fb;
+        for (; t < tc; ++t) {   // (one wavefront holds the last, partial batch)
+            NodeBatch<1> nb;
+            nb.load(nodes, t0 + t);
+            uint32_t m[1];
+            shallow_leaf4<D, 1>(xquad, nb, m);
+            s_m[t * kWave + lane] = m[0];
         }
+        __syncthreads();
+        if (threadIdx.x < kSplitEvents) {
+            const uint8_t *mine = reinterpret_cast<const uint8_t *>(s_m) + threadIdx.x;
+            int q = 0;
+            for (; q + 8 <= tc; q += 8) {
+                double l[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    l[u] = leaf_at(s_leaf + (q + u) * NLEAF, mine[(q + u) * kSplitEvents], 0);
+#pragma unroll
+                for (int u = 0; u < 8; ++u) F += l[u];
+            }
+            for (; q < tc; ++q) F += leaf_at(s_leaf + q * NLEAF, mine[q * kSplitEvents], 0);
+        }
+    }
+    const int64_t i = base + threadIdx.x;
+    if (threadIdx.x < kSplitEvents && i < n) {
+        prob[i] = (float)(1.0 / (1.0 + exp(-2.0 * F)));
+        if (score) score[i] = F;
     }
 }
 
@@ -2672,7 +2835,6 @@ __global__ __launch_bounds__(1024) void apply_float_kernel(
 constexpr int kEncodeThreads = 256;
 constexpr int kEncodeVecs = 2;
 constexpr int kEncodeTile = kEncodeThreads * kEncodeVecs * 4;
-typedef float float4_unaligned __attribute__((ext_vector_type(4), aligned(4)));
 __global__ __launch_bounds__(kEncodeThreads) void encode_kernel(
     const float *__restrict__ x, int64_t ldx, int64_t n, const float *__restrict__ bounds,
     int nbins, uint8_t *__restrict__ xb, int64_t ldb, int *__restrict__ err,
@@ -2842,6 +3004,12 @@ hipError_t prepare_kernels(size_t max_lds) {
                             allow_lds(apply_shallow_kernel<1, true>, max_lds),
                             allow_lds(apply_shallow_kernel<2, true>, max_lds),
                             allow_lds(apply_shallow_kernel<3, true>, max_lds),
+                            allow_lds(apply_split_kernel<1, false>, max_lds),
+                            allow_lds(apply_split_kernel<2, false>, max_lds),
+                            allow_lds(apply_split_kernel<3, false>, max_lds),
+                            allow_lds(apply_split_kernel<1, true>, max_lds),
+                            allow_lds(apply_split_kernel<2, true>, max_lds),
+                            allow_lds(apply_split_kernel<3, true>, max_lds),
                             allow_lds(apply_float_kernel<1>, max_lds),
                             allow_lds(apply_float_kernel<2>, max_lds),
                             allow_lds(apply_float_kernel<3>, max_lds),
@@ -3437,7 +3605,7 @@ hipError_t launch_route(const uint8_t *xb, int64_t ldb, int64_t n, int d, uint8_
 }
 
 ApplyShape plan_apply(int64_t n, int d_used, int n_trees, int depth, bool missing,
-                      int cu_count, size_t max_lds, int threads) {
+                      int cu_count, size_t max_lds, int threads, size_t extra_lds) {
     ApplyShape as{};
     as.d_used = d_used;
     as.missing = missing;
@@ -3445,20 +3613,62 @@ ApplyShape plan_apply(int64_t n, int d_used, int n_trees, int depth, bool missin
     const int nin = (1 << depth) - 1, nleaf = missing ? 2 * nin + 1 : 1 << depth;
     const size_t lds_cap = max_lds > kHistStaticLdsReserve ? max_lds - kHistStaticLdsReserve : 0;
     as.shallow = depth <= kApplyShallowDepth && !missing;
-    if (as.shallow) {
-        // workgroups of 512 threads (two per CU for 40 features and 400
-        // trees of depth 3, measured best); the tile of codes takes at most
-        // 96 KiB, the leaf values of as many trees as fit the rest
-        int t = threads > 0 ? threads : 512;
-        while (t > 64 && (size_t)d_used * (2 * t + 8) > 96 * 1024) t -= 64;
-        as.threads = t;
-        const size_t xtile = (size_t)d_used * (2 * t + 8);
-        const size_t room = lds_cap > xtile + 64 ? lds_cap - xtile - 64 : 0;
-        int64_t tpc = (int64_t)(room / ((size_t)nleaf * 8));
-        if (tpc < 1) tpc = 1;
+    const size_t leaf_bytes = (size_t)nleaf * 8;
+    if (as.shallow && threads <= 0 && n <= (int64_t)kSplitEvents * kSplitRounds * cu_count &&
+        (size_t)d_used * kSplitEvents + extra_lds + 64 + leaf_bytes + kWave * 4 <= lds_cap) {
+        // few events: the wavefronts of a workgroup share the trees
+        as.split = true;
+        as.threads = kSplitThreads;
+        as.node_stride = kSplitEvents;
+        const size_t xtile = (size_t)d_used * kSplitEvents + extra_lds;
+        int64_t tpc = (int64_t)((lds_cap - xtile - 64) / (leaf_bytes + kWave * 4));
         if (tpc > n_trees) tpc = n_trees;
+        if (tpc < n_trees) tpc = tpc > kApplyBatch ? tpc / kApplyBatch * kApplyBatch : tpc;
         as.trees_per_chunk = (int)tpc;
-        as.lds_bytes = (size_t)tpc * nleaf * 8 + xtile;
+        as.lds_bytes = (size_t)tpc * (leaf_bytes + kWave * 4) + xtile;
+        as.blocks = (int)((n + kSplitEvents - 1) / kSplitEvents);
+        return as;
+    }
+    if (as.shallow) {
+        // the workgroup size and workgroups per CU of least rounds x time.  A
+        // round of W wavefronts per CU takes about 6.5 + 0.75 W (W = 24 most,
+        // at least 12 in these units of 7 us for 400 trees): the traversal needs
+        // three or more wavefronts per SIMD to keep the vector units busy (10M
+        // events of 40 features: 1.58 ms with 8 per CU, 1.33 ms with 12; of 8
+        // features: 1.02 ms with 24, 1.07 ms with 32).  A workgroup holds its
+        // tile of codes and all leaf values, or at least 16 KiB of them at a time.
+        const int64_t all = (int64_t)n_trees * (int64_t)leaf_bytes;
+        const int64_t least = std::min<int64_t>(all, 16384);
+        double best = 0.0;
+        int best_t = 0, best_w = 1;
+        for (int w = 1; w <= 4; ++w)
+            for (int t = 256; t <= 1024 && w * t <= 24 * kWave; t += 256) {
+                const int64_t room = (int64_t)(max_lds / w) - (int64_t)kHistStaticLdsReserve -
+                                     64 - (int64_t)extra_lds - (int64_t)d_used * 4 * t;
+                if (room < least) continue;
+                const int64_t round = 4 * (int64_t)t * w * cu_count;
+                const double cost = (double)((n + round - 1) / round) *
+                                    std::max(12.0, 6.5 + 0.75 * (w * t / kWave));
+                if (best == 0.0 || cost < best) {
+                    best = cost;
+                    best_t = t;
+                    best_w = w;
+                }
+            }
+        int t = threads > 0 ? threads : best_t > 0 ? best_t : 256;
+        while (t > 64 && (size_t)d_used * 4 * t + leaf_bytes + extra_lds + 64 > lds_cap) t -= 64;
+        as.threads = t;
+        as.node_stride = 4 * t;
+        const size_t xtile = (size_t)d_used * 4 * t + extra_lds;
+        const size_t cap = best_t > 0 && threads <= 0 ? max_lds / best_w - kHistStaticLdsReserve
+                                                      : lds_cap;
+        const size_t room = cap > xtile + 64 ? cap - xtile - 64 : 0;
+        int64_t tpc = std::min<int64_t>(n_trees, (int64_t)(room / leaf_bytes));
+        if (tpc < n_trees) tpc = tpc / kApplyBatch * kApplyBatch;
+        if (tpc < 1) tpc = 1;
+        as.trees_per_chunk = (int)tpc;
+        as.lds_bytes = (size_t)tpc * leaf_bytes + xtile;
+        as.per_cu = threads > 0 ? 2 : best_w;
     } else {
         // 768 threads (512 for depth 4) measured best on 8M events x 40
         // features: two workgroups per CU keep 24 wavefronts resident
@@ -3478,9 +3688,9 @@ ApplyShape plan_apply(int64_t n, int d_used, int n_trees, int depth, bool missin
         as.lds_bytes =
             (size_t)tpc * nleaf * 8 + ((((size_t)tpc * nin) + 3) & ~(size_t)3) * 2 + xtile;
     }
-    const int64_t tile_events = as.shallow ? 2 * (int64_t)as.threads : as.threads;
+    const int64_t tile_events = as.shallow ? 4 * (int64_t)as.threads : as.threads;
     const int64_t ntiles = (n + tile_events - 1) / tile_events;
-    int64_t blocks = (int64_t)cu_count * (as.shallow ? 4 : 8);
+    int64_t blocks = (int64_t)cu_count * (as.shallow ? as.per_cu : 8);
     if (blocks > ntiles) blocks = ntiles;
     if (blocks < 1) blocks = 1;
     as.blocks = (int)blocks;
@@ -3494,9 +3704,14 @@ hipError_t launch_apply(const ApplyShape &as, const uint8_t *xb, int64_t ldb, in
     if (as.shallow) {
         if (!nodes) return hipErrorInvalidValue;
 #define FBDT_APPLY_S(DV)                                                                        \
-    apply_shallow_kernel<DV, false><<<as.blocks, as.threads, as.lds_bytes, s>>>(                \
-        xb, ldb, nullptr, 0, nullptr, 0, n, as.d_used, nodes, leaves, n_trees,                 \
-        as.trees_per_chunk, f0, prob, score)
+    if (as.split)                                                                               \
+        apply_split_kernel<DV, false><<<as.blocks, as.threads, as.lds_bytes, s>>>(              \
+            xb, ldb, nullptr, 0, nullptr, 0, n, as.d_used, nodes, leaves, n_trees,              \
+            as.trees_per_chunk, f0, prob, score);                                               \
+    else                                                                                        \
+        apply_shallow_kernel<DV, false><<<as.blocks, as.threads, as.lds_bytes, s>>>(            \
+            xb, ldb, nullptr, 0, nullptr, 0, n, as.d_used, nodes, leaves, n_trees,              \
+            as.trees_per_chunk, f0, prob, score)
         switch (depth) {
         case 1: FBDT_APPLY_S(1); break;
         case 2: FBDT_APPLY_S(2); break;
@@ -3555,11 +3770,8 @@ ApplyShape plan_apply_float(int64_t n, int d_used, int n_trees, int depth, bool 
     if (depth <= kApplyShallowDepth && !missing) {
         // the binned shallow traversal, its tile staged from the values with
         // the threshold table beside it in LDS
-        const size_t tb = (table_bytes + 15) & ~(size_t)15;
-        ApplyShape as = plan_apply(n, d_used, n_trees, depth, false, cu_count,
-                                   max_lds > tb ? max_lds - tb : 0, threads);
-        as.lds_bytes += tb;
-        return as;
+        return plan_apply(n, d_used, n_trees, depth, false, cu_count, max_lds, threads,
+                          (table_bytes + 15) & ~(size_t)15);
     }
     ApplyShape as{};
     as.d_used = d_used;
@@ -3596,9 +3808,14 @@ hipError_t launch_apply_float(const ApplyShape &as, const float *x, int64_t ldx,
     if (as.shallow) {
         if (!fnodes || !ftab) return hipErrorInvalidValue;
 #define FBDT_APPLY_FS(DV)                                                                       \
-    apply_shallow_kernel<DV, true><<<as.blocks, as.threads, as.lds_bytes, s>>>(                 \
-        nullptr, 0, x, ldx, ftab, ftab_words, n, as.d_used, fnodes, leaves, n_trees,           \
-        as.trees_per_chunk, f0, prob, score)
+    if (as.split)                                                                               \
+        apply_split_kernel<DV, true><<<as.blocks, as.threads, as.lds_bytes, s>>>(               \
+            nullptr, 0, x, ldx, ftab, ftab_words, n, as.d_used, fnodes, leaves, n_trees,        \
+            as.trees_per_chunk, f0, prob, score);                                               \
+    else                                                                                        \
+        apply_shallow_kernel<DV, true><<<as.blocks, as.threads, as.lds_bytes, s>>>(             \
+            nullptr, 0, x, ldx, ftab, ftab_words, n, as.d_used, fnodes, leaves, n_trees,        \
+            as.trees_per_chunk, f0, prob, score)
         switch (depth) {
         case 1: FBDT_APPLY_FS(1); break;
         case 2: FBDT_APPLY_FS(2); break;

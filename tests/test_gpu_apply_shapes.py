@@ -1,0 +1,64 @@
+"""Traversals of shallow forests at the edges of their launch shapes: lanes of
+four events, the few-events kernel and its limit, chunks of trees, one to
+255 features, and outputs that start at any element."""
+import numpy as np
+import pytest
+import torch
+
+import paper_1609_06119_amd as fb
+from oracle import fbdt_oracle as O
+from synth import random_forest
+
+pytestmark = pytest.mark.gpu
+
+
+def _model(f, d, B, bounds=None):
+    return fb.Model.from_arrays(f["cut_feature"], f["cut_bin"], f["leaf"], f["f0"], d, B,
+                                boundaries=bounds)
+
+
+@pytest.mark.parametrize("n,d,B,D,T", [
+    (1, 1, 2, 1, 1), (3, 40, 256, 3, 3), (255, 7, 256, 2, 5), (256, 7, 17, 3, 66),
+    (257, 255, 256, 3, 9), (1021, 40, 256, 3, 700), (5, 255, 256, 1, 2500),
+    (393_216, 5, 256, 3, 5), (393_217, 5, 256, 3, 5), (500_003, 40, 256, 2, 7),
+    (400_001, 255, 64, 3, 6), (410_003, 3, 256, 3, 600), (420_001, 11, 256, 1, 13),
+    (1_000_001, 36, 256, 3, 300),
+])
+def test_shallow_apply(n, d, B, D, T):
+    rng = np.random.default_rng([n, d, T])
+    f = random_forest(T, D, d, B, n + T)
+    xb = rng.integers(0, B, (d, n)).astype(np.uint8)
+    om = O.Model(D, B, d, f["f0"], f["cut_feature"], f["cut_bin"], np.zeros_like(f["leaf"]),
+                 f["leaf"])
+    p, F = O.apply(om, xb)
+    out = torch.empty(n + 3, device="cuda")
+    score = torch.empty(n, dtype=torch.float64, device="cuda")
+    # values whose codes are xb: boundary k at k + 1, value = code + 1/2
+    bounds = np.repeat(np.arange(1, B, dtype=np.float32)[None], d, axis=0)
+    m = _model(f, d, B, bounds)
+    got = fb.apply(m, fb.Codes.from_numpy(xb), prob=out[3:], score=score)
+    assert np.array_equal(score.cpu().numpy(), F)
+    assert np.allclose(got.cpu().numpy(), p, rtol=0, atol=6e-8)
+    x = torch.zeros(d, n + 5, device="cuda")[:, 1:n + 1]   # rows of an odd start and stride
+    x.copy_(torch.from_numpy(xb).float() + 0.5)
+    score.zero_()
+    got = fb.apply_float(m, x, prob=out[1:n + 1], score=score)
+    assert np.array_equal(score.cpu().numpy(), F)
+    assert np.allclose(got.cpu().numpy(), p, rtol=0, atol=6e-8)
+
+
+def test_calls_of_few_and_many_events_interleave():
+    """Both kernels' node records stay in place for launches still queued."""
+    d, B, D, T = 40, 256, 3, 400
+    f = random_forest(T, D, d, B, 3)
+    m = _model(f, d, B)
+    xb = torch.randint(0, B, (d, 1_000_000), dtype=torch.uint8, device="cuda")
+    big = fb.Codes(xb, 1_000_000)
+    few = fb.Codes(xb[:, :512].contiguous(), 500)
+    p_big, p_few = fb.apply(m, big), fb.apply(m, few)
+    torch.cuda.synchronize()
+    runs = [(fb.apply(m, big), fb.apply(m, few)) for _ in range(4)]
+    torch.cuda.synchronize()
+    for a, b in runs:
+        assert torch.equal(a, p_big) and torch.equal(b, p_few)
+    assert torch.equal(p_few, p_big[:500])
