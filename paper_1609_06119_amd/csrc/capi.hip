@@ -33,19 +33,19 @@ struct fbdt_model {
         int device;
         uint16_t *cuts;
         double *leaves;
-        // [T][16] node records of shallow forests, or null, and the tile stride
-        // they were made for: [1] for launches that split the trees, so that
-        // calls of few and of many events, which may overlap, do not share any
-        int nodes_stride[2];
-        uint32_t *nodes[2];
-        uint2 *frec;        // [T][2^D - 1] (feature, threshold) for float apply, or null
         double *gains;      // [T][2^D - 1] separation gains, or null
-        // float apply of shallow forests: per-feature threshold table and the
-        // node records (threshold ranks) for the tile stride fnodes_stride
+        // float apply: per-feature threshold table, or null
         uint32_t *ftab;
         int ftab_words;
-        uint32_t *fnodes[2];
-        int fnodes_stride[2];
+        // node records, or null, and the tile stride they were made for (0:
+        // none), of binned [0] and float [1] input, for launches that take the
+        // bulk [0] and the few-events kernel [1]: calls of both kinds may overlap
+        // and share none
+        struct Records {
+            int stride;
+            uint32_t *nodes;   // [T][16] (depth <= 3, or the first three levels)
+            uint32_t *recs;    // [T][2^D - 1] (deep kernels)
+        } rec[2][2];
     };
     std::mutex mu;
     std::vector<DeviceCopy> copies;
@@ -369,6 +369,38 @@ double list_algorithmic_bytes(int64_t n, double alpha, int d, int n_bins, int la
     const double entries = alpha * (double)n * (sib ? 0.5 : 1.0);
     const int hnodes = sib ? 1 << (layer - 1) : 1 << layer;
     return entries * (8.0 + d) + (double)hnodes * d * n_bins * 2 * 8;
+}
+
+// The node records of a launch shape, made on first use: `cut` gives a
+// node's bin, or the rank of its threshold.  Call with m->mu held.
+template <typename Cut>
+int make_records(const fbdt_model *m, const ApplyShape &as, const Cut &cut,
+                        fbdt_model::DeviceCopy::Records &r) {
+    const uint32_t xs = (uint32_t)apply_node_stride(as);
+    if (r.stride == (int)xs) return FBDT_OK;
+    const size_t T = m->n_trees, nin = ((size_t)1 << m->depth) - 1;
+    if (as.shallow || !m->missing) {
+        const size_t top = std::min<size_t>(nin, 7);
+        std::vector<uint32_t> table(T * 16, 0u);
+        for (size_t t = 0; t < T; ++t)
+            for (size_t k = 0; k < top; ++k) {
+                const size_t q = t * nin + k;
+                table[t * 16 + k] = (uint32_t)m->cut_feature[q] * xs;
+                table[t * 16 + 8 + k] = (256u - cut(q)) * 0x01010101u;
+            }
+        if (!r.nodes)
+            HIP_TRY(device_alloc(reinterpret_cast<void **>(&r.nodes), table.size() * 4));
+        HIP_TRY(hipMemcpy(r.nodes, table.data(), table.size() * 4, hipMemcpyHostToDevice));
+    }
+    if (!as.shallow) {
+        std::vector<uint32_t> table(T * nin);
+        for (size_t q = 0; q < table.size(); ++q)
+            table[q] = (uint32_t)m->cut_feature[q] * xs << 8 | cut(q);
+        if (!r.recs) HIP_TRY(device_alloc(reinterpret_cast<void **>(&r.recs), table.size() * 4));
+        HIP_TRY(hipMemcpy(r.recs, table.data(), table.size() * 4, hipMemcpyHostToDevice));
+    }
+    r.stride = (int)xs;
+    return FBDT_OK;
 }
 
 }  // namespace
@@ -1084,6 +1116,12 @@ int fbdt_model_import(const fbdt_model_view *v, fbdt_model **out) {
     return FBDT_OK;
 }
 
+static void free_records(fbdt_model::DeviceCopy::Records &r) {
+    if (r.nodes) (void)hipFree(r.nodes);
+    if (r.recs) (void)hipFree(r.recs);
+    r = {};
+}
+
 int fbdt_model_set_boundaries(fbdt_model *m, const float *boundaries) {
     int rc;
     if (!m || !boundaries) return fail(FBDT_E_INVAL, "NULL argument");
@@ -1095,16 +1133,10 @@ int fbdt_model_set_boundaries(fbdt_model *m, const float *boundaries) {
     (void)hipGetDevice(&cur);
     for (auto &c : m->copies)
         if (hipSetDevice(c.device) == hipSuccess) {
-            if (c.frec) (void)hipFree(c.frec);
             if (c.ftab) (void)hipFree(c.ftab);
-            for (int q = 0; q < 2; ++q) {
-                if (c.fnodes[q]) (void)hipFree(c.fnodes[q]);
-                c.fnodes[q] = nullptr;
-                c.fnodes_stride[q] = 0;
-            }
-            c.frec = nullptr;
             c.ftab = nullptr;
             c.ftab_words = 0;
+            for (auto &r : c.rec[1]) free_records(r);
         }
     if (cur >= 0) (void)hipSetDevice(cur);
     return FBDT_OK;
@@ -1118,13 +1150,10 @@ void fbdt_model_free(fbdt_model *m) {
         if (hipSetDevice(c.device) == hipSuccess) {
             (void)hipFree(c.cuts);
             (void)hipFree(c.leaves);
-            if (c.frec) (void)hipFree(c.frec);
             if (c.gains) (void)hipFree(c.gains);
             if (c.ftab) (void)hipFree(c.ftab);
-            for (int q = 0; q < 2; ++q) {
-                if (c.nodes[q]) (void)hipFree(c.nodes[q]);
-                if (c.fnodes[q]) (void)hipFree(c.fnodes[q]);
-            }
+            for (auto &kind : c.rec)
+                for (auto &r : kind) free_records(r);
         }
     }
     if (cur >= 0) (void)hipSetDevice(cur);
@@ -1188,41 +1217,26 @@ int fbdt_apply(const fbdt_model *mc, const uint8_t *xb, int64_t n, int32_t d, in
     if ((rc = current_device(&dev, &di))) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int T = m->n_trees, D = m->depth;
-    const size_t nin = ((size_t)1 << D) - 1;
-    ApplyShape as = plan_apply(n, m->n_features, T, D, m->missing, di.cu_count, di.max_lds,
-                               (int)opt_apply_threads.load());
+    const ApplyShape as = plan_apply(n, m->n_features, T, D, m->missing, di.cu_count, di.max_lds,
+                                     (int)opt_apply_threads.load());
     if (as.lds_bytes + kHistStaticLdsReserve > di.max_lds)
         return fail(FBDT_E_INVAL, "apply needs %zu bytes of LDS, the device has %zu (fewer "
                     "apply_threads)", as.lds_bytes, di.max_lds);
-    uint16_t *cuts = nullptr;
-    uint32_t *nodes = nullptr;
-    double *leaves = nullptr;
+    fbdt_model::DeviceCopy::Records r{};
+    const double *leaves = nullptr;
     {
         std::lock_guard<std::mutex> lk(m->mu);
         fbdt_model::DeviceCopy *copy = nullptr;
         if ((rc = device_copy(m, dev, &copy))) return rc;
-        if (as.shallow && copy->nodes_stride[as.split] != apply_node_stride(as)) {
-            // node records for this launch's tile stride
-            const int xs = apply_node_stride(as);
-            std::vector<uint32_t> table((size_t)T * 16, 0u);
-            for (size_t t = 0; t < (size_t)T; ++t)
-                for (size_t k = 0; k < nin; ++k) {
-                    table[t * 16 + k] = (uint32_t)m->cut_feature[t * nin + k] * (uint32_t)xs;
-                    table[t * 16 + 8 + k] = (256u - m->cut_bin[t * nin + k]) * 0x01010101u;
-                }
-            if (!copy->nodes[as.split])
-                HIP_TRY(device_alloc(reinterpret_cast<void **>(&copy->nodes[as.split]),
-                                     table.size() * sizeof(uint32_t)));
-            HIP_TRY(hipMemcpy(copy->nodes[as.split], table.data(), table.size() * sizeof(uint32_t),
-                              hipMemcpyHostToDevice));
-            copy->nodes_stride[as.split] = xs;
-        }
-        cuts = copy->cuts;
-        nodes = copy->nodes[as.split];
+        if ((rc = make_records(m, as, [&](size_t q) { return (uint32_t)m->cut_bin[q]; },
+                               copy->rec[0][as.split])))
+            return rc;
+        r = copy->rec[0][as.split];
         leaves = copy->leaves;
     }
     Timed tm(FBDT_K_APPLY, s, (double)n * (m->n_features + 4));
-    HIP_TRY(launch_apply(as, xb, ldb, n, cuts, nodes, leaves, T, D, m->f0, prob, score, s));
+    HIP_TRY(launch_apply(as, ApplyInput{n, xb, ldb, nullptr, 0, nullptr, 0}, r.nodes, r.recs, leaves,
+                         T, D, m->f0, prob, score, s));
     tm.done();
     return FBDT_OK;
 }
@@ -1292,10 +1306,9 @@ int fbdt_apply_float(const fbdt_model *mc, const float *x, int64_t n, int32_t d,
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int T = m->n_trees, D = m->depth;
     const size_t nin = ((size_t)1 << D) - 1;
-    const bool shallow = D <= kApplyShallowDepth && !m->missing;
     ApplyShape as{};
-    const uint2 *rec = nullptr;
-    const uint32_t *fnodes = nullptr, *ftab = nullptr;
+    fbdt_model::DeviceCopy::Records r{};
+    const uint32_t *ftab = nullptr;
     int ftab_words = 0;
     const double *leaves = nullptr;
     {
@@ -1324,7 +1337,7 @@ int fbdt_apply_float(const fbdt_model *mc, const float *x, int64_t n, int32_t d,
                         v.end());
             }
         };
-        if (shallow && !copy->ftab) {
+        if (!copy->ftab) {
             collect();
             const size_t d_used = m->n_features;
             std::vector<uint32_t> table(d_used, 0u);
@@ -1347,61 +1360,25 @@ int fbdt_apply_float(const fbdt_model *mc, const float *x, int64_t n, int32_t d,
                               hipMemcpyHostToDevice));
             copy->ftab_words = (int)table.size();
         }
-        if (shallow) {
-            as = plan_apply_float(n, m->n_features, T, D, false, di.cu_count, di.max_lds,
-                                  (int)opt_apply_threads.load(),
-                                  (size_t)copy->ftab_words * sizeof(uint32_t));
-            if (copy->fnodes_stride[as.split] != apply_node_stride(as)) {
-                // node records for this launch's tile stride, with threshold ranks
-                collect();
-                const int xs = apply_node_stride(as);
-                std::vector<uint32_t> table((size_t)T * 16, 0u);
-                for (size_t t = 0; t < (size_t)T; ++t)
-                    for (size_t k = 0; k < nin; ++k) {
-                        const size_t q = t * nin + k;
-                        const uint32_t f = m->cut_feature[q];
-                        const auto &v = per[f];
-                        const uint32_t r = (uint32_t)(std::lower_bound(v.begin(), v.end(),
-                                                                       threshold(q)) - v.begin()) + 1u;
-                        table[t * 16 + k] = f * (uint32_t)xs;
-                        table[t * 16 + 8 + k] = (256u - r) * 0x01010101u;
-                    }
-                if (!copy->fnodes[as.split])
-                    HIP_TRY(device_alloc(reinterpret_cast<void **>(&copy->fnodes[as.split]),
-                                         table.size() * sizeof(uint32_t)));
-                HIP_TRY(hipMemcpy(copy->fnodes[as.split], table.data(), table.size() * sizeof(uint32_t),
-                                  hipMemcpyHostToDevice));
-                copy->fnodes_stride[as.split] = xs;
-            }
-            fnodes = copy->fnodes[as.split];
-            ftab = copy->ftab;
-            ftab_words = copy->ftab_words;
-        } else {
-            as = plan_apply_float(n, m->n_features, T, D, m->missing, di.cu_count, di.max_lds,
-                                  (int)opt_apply_threads.load(), 0);
-            if (!copy->frec) {
-                std::vector<uint2> table((size_t)T * nin);
-                for (size_t k = 0; k < table.size(); ++k) {
-                    const float thr = threshold(k);
-                    uint32_t bits;
-                    std::memcpy(&bits, &thr, sizeof bits);
-                    table[k] = make_uint2(m->cut_feature[k], bits);
-                }
-                HIP_TRY(device_alloc(reinterpret_cast<void **>(&copy->frec),
-                                     table.size() * sizeof(uint2)));
-                HIP_TRY(hipMemcpy(copy->frec, table.data(), table.size() * sizeof(uint2),
-                                  hipMemcpyHostToDevice));
-            }
-            rec = copy->frec;
-        }
+        as = plan_apply(n, m->n_features, T, D, m->missing, di.cu_count, di.max_lds,
+                        (int)opt_apply_threads.load(), (size_t)copy->ftab_words * sizeof(uint32_t));
+        if (as.lds_bytes + kHistStaticLdsReserve > di.max_lds)
+            return fail(FBDT_E_INVAL, "apply needs %zu bytes of LDS, the device has %zu (fewer "
+                        "apply_threads)", as.lds_bytes, di.max_lds);
+        auto rank = [&](size_t q) {
+            collect();
+            const auto &v = per[m->cut_feature[q]];
+            return (uint32_t)(std::lower_bound(v.begin(), v.end(), threshold(q)) - v.begin()) + 1u;
+        };
+        if ((rc = make_records(m, as, rank, copy->rec[1][as.split]))) return rc;
+        r = copy->rec[1][as.split];
+        ftab = copy->ftab;
+        ftab_words = copy->ftab_words;
         leaves = copy->leaves;
     }
-    if (as.lds_bytes + kHistStaticLdsReserve > di.max_lds)
-        return fail(FBDT_E_INVAL, "apply needs %zu bytes of LDS, the device has %zu (fewer "
-                    "apply_threads)", as.lds_bytes, di.max_lds);
     Timed tm(FBDT_K_APPLY, s, (double)n * (4.0 * m->n_features + 4));
-    HIP_TRY(launch_apply_float(as, x, ldx, n, rec, fnodes, ftab, ftab_words, leaves, T, D, m->f0,
-                               prob, score, s));
+    HIP_TRY(launch_apply(as, ApplyInput{n, nullptr, 0, x, ldx, ftab, ftab_words}, r.nodes, r.recs,
+                         leaves, T, D, m->f0, prob, score, s));
     tm.done();
     return FBDT_OK;
 }

@@ -412,36 +412,53 @@ hipError_t launch_hist_list(const ListShape &ls, int lmode, const uint2 *list,
                             bool signed_w, int scale, uint2 *lchunks, uint64_t *partial, int *err,
                             uint32_t *cnt_out, hipStream_t s);
 
-// Forest traversal.  cuts: [T][2^D-1] packed (feature | bin << 8), for the
-// general kernel; nodes: [T][16] for depth <= kApplyShallowDepth, for heap
-// node k + 1 word k = feature * apply_node_stride (the LDS row offset in the
-// launch's code tile) and word 8 + k = (256 - bin) * 0x01010101.
+// Forest traversal.  Forests of depth <= kApplyShallowDepth without missing
+// values take the shallow kernels, others the deep ones.  nodes (depth <= 3,
+// and the first three levels of deeper trees without missing values): [T][16],
+// for heap node k + 1 word k = feature * apply_node_stride (the LDS row offset
+// in the launch's code tile) and word 8 + k = (256 - bin) * 0x01010101.  recs
+// (deep kernels): [T][2^D - 1], feature * apply_node_stride << 8 | bin.
 constexpr int kApplyShallowDepth = 3;
-// Rounds of one workgroup per CU up to which the shallow traversal shares the
-// trees of 256 events among a workgroup's wavefronts: a round takes 14 us for
-// 400 trees of depth 3 over 40 features, a round of the bulk kernel 84 to 100
-// us (of 2,048 or 3,072 events per CU).
+// Rounds of one workgroup per CU up to which a traversal shares the trees of
+// 256 events among a workgroup's wavefronts: a round takes 14 us for 400 trees
+// of depth 3 over 40 features, a round of the bulk kernel 84 to 100 us (of
+// 2,048 or 3,072 events per CU).
 constexpr int kSplitRounds = 6;
 struct ApplyShape {
-    bool shallow;          // depth <= kApplyShallowDepth: apply_shallow_kernel
-    bool split;            // apply_split_kernel instead
+    bool shallow;          // the shallow kernels
+    bool split;            // the kernel for few events
     bool missing;          // missing values: boost weights of every node per tree (heap
                            // order) and the missing code stops an event at its node
     int threads;
     int blocks;
-    int trees_per_chunk;   // trees whose leaf values (and cuts) are staged in LDS at once
+    int trees_per_chunk;   // trees whose weights (and records) are staged in LDS at once
     int d_used;
-    int per_cu;            // workgroups per CU (shallow)
-    int node_stride;       // bytes between the features' rows in the code tile (shallow)
+    int node_stride;       // bytes between the features' rows in the code tile
     size_t lds_bytes;
 };
+// table_bytes: the threshold table of a float input (0: binned).
 ApplyShape plan_apply(int64_t n, int d_used, int n_trees, int depth, bool missing,
-                      int cu_count, size_t max_lds, int threads, size_t extra_lds = 0);
+                      int cu_count, size_t max_lds, int threads, size_t table_bytes = 0);
 inline int apply_node_stride(const ApplyShape &as) { return as.node_stride; }
-hipError_t launch_apply(const ApplyShape &as, const uint8_t *xb, int64_t ldb, int64_t n,
-                        const uint16_t *cuts, const uint32_t *nodes, const double *leaves,
-                        int n_trees, int depth, double f0, float *prob, double *score,
-                        hipStream_t s);
+// Events: binned codes (xb, ldb), or float32 values (xf != null) with the
+// thresholds that the forest's cuts test: ftab = [d_used] words offset << 8 |
+// levels, then per feature, from its offset, 2^levels words: the ascending
+// distinct thresholds (float bits) level by level (entry 2^l + p decides bit l
+// of the codes that start with p; NaN where there is none), ftab_words words
+// in all.  The records then carry the rank (from 1) of a node's threshold among
+// its feature's in place of the bin.
+struct ApplyInput {
+    int64_t n;
+    const uint8_t *xb;
+    int64_t ldb;
+    const float *xf;
+    int64_t ldx;
+    const uint32_t *ftab;
+    int ftab_words;
+};
+hipError_t launch_apply(const ApplyShape &as, const ApplyInput &in, const uint32_t *nodes,
+                        const uint32_t *recs, const double *leaves, int n_trees, int depth,
+                        double f0, float *prob, double *score, hipStream_t s);
 
 // Per-event importance [d_out][ldi] (float64) of binned events: the gains of
 // the nodes on each event's path summed per cut feature, tree by tree.
@@ -451,24 +468,6 @@ ApplyShape plan_importance(int64_t n, int d_used, int n_trees, int depth, bool m
 hipError_t launch_importance(const ApplyShape &as, const uint8_t *xb, int64_t ldb, int64_t n,
                              const uint16_t *cuts, const double *gains, int n_trees, int depth,
                              double *imp, int64_t ldi, int d_out, hipStream_t s);
-
-// Traversal of float32 events [d][ldx] with value thresholds.  Forests of
-// depth <= kApplyShallowDepth without missing values (as.shallow) take the
-// binned shallow traversal with its code tile staged from the values:
-// ftab = [d_used] words offset << 8 | levels, then per feature, from its
-// offset, 2^levels words: the ascending distinct thresholds its cuts test
-// (float bits) level by level (entry 2^l + p decides bit l of the codes that
-// start with p; NaN where there is none), ftab_words words in all (table_bytes
-// of LDS); fnodes = node records as for the binned traversal (stride
-// apply_node_stride(as)) with word 8 + k = (256 - c') * 0x01010101, c' the rank
-// (from 1) of the node's threshold among its feature's.  Other forests walk
-// rec: [T][2^D-1] (feature, float bits of the threshold) per heap node.
-ApplyShape plan_apply_float(int64_t n, int d_used, int n_trees, int depth, bool missing,
-                            int cu_count, size_t max_lds, int threads, size_t table_bytes);
-hipError_t launch_apply_float(const ApplyShape &as, const float *x, int64_t ldx, int64_t n,
-                              const uint2 *rec, const uint32_t *fnodes, const uint32_t *ftab,
-                              int ftab_words, const double *leaves, int n_trees, int depth,
-                              double f0, float *prob, double *score, hipStream_t s);
 
 // Equal-frequency boundaries on the device: for every feature the value of
 // rank floor(k m / B), k = 1 .. B - 1, among its m non-NaN values, found by

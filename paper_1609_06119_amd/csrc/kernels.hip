@@ -2303,67 +2303,6 @@ __global__ __launch_bounds__(256) void route_kernel(const uint8_t *__restrict__ 
 }
 
 // ---------------------------------------------------------------------------
-// Forest traversal.  A workgroup stages a tile of `blockDim.x` events (all
-// model features, padded rows to spread LDS banks) and a chunk of trees in
-// LDS; each thread walks its event through every tree (left = bin < cut,
-// Fig. 1), adds the leaf's boost weight to F in float64 in tree order, and
-// writes 1 / (1 + exp(-2F)) as float32.
-__global__ __launch_bounds__(1024) void apply_kernel(
-    const uint8_t *__restrict__ xb, int64_t ldb, int64_t n, int d_used,
-    const uint16_t *__restrict__ cuts, const double *__restrict__ leaves, int T, int depth,
-    bool missing, int tpc, double f0, float *__restrict__ prob, double *__restrict__ score) {
-    extern __shared__ double smem[];
-    const int nin = (1 << depth) - 1;
-    // boost weights per tree: the leaves, or with missing values (section
-    // 4.2) every node in heap order, for events that stop at an inner node
-    const int nleaf = missing ? 2 * nin + 1 : 1 << depth;
-    const int first_id = missing ? 1 : 1 << depth;
-    double *s_leaf = smem;
-    uint16_t *s_cut = reinterpret_cast<uint16_t *>(s_leaf + (size_t)tpc * nleaf);
-    uint8_t *s_x = reinterpret_cast<uint8_t *>(s_cut + (((size_t)tpc * nin + 3) & ~(size_t)3));
-    const int XS = blockDim.x + 4;
-    const int nchunks = (T + tpc - 1) / tpc;
-    const int64_t ntiles = (n + blockDim.x - 1) / blockDim.x;
-    bool staged = false;
-    for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const int64_t i = tile * blockDim.x + threadIdx.x;
-        __syncthreads();
-        for (int f = 0; f < d_used; ++f)
-            s_x[f * XS + threadIdx.x] = i < n ? xb[(int64_t)f * ldb + i] : 0;
-        double Fv = f0;
-        for (int ch = 0; ch < nchunks; ++ch) {
-            const int t0 = ch * tpc;
-            const int tc = min(tpc, T - t0);
-            if (nchunks > 1 || !staged) {
-                __syncthreads();
-                for (int q = threadIdx.x; q < tc * nleaf; q += blockDim.x)
-                    s_leaf[q] = leaves[(size_t)t0 * nleaf + q];
-                for (int q = threadIdx.x; q < tc * nin; q += blockDim.x)
-                    s_cut[q] = cuts[(size_t)t0 * nin + q];
-                staged = true;
-            }
-            __syncthreads();
-            for (int t = 0; t < tc; ++t) {
-                int node = 1;
-                for (int lvl = 0; lvl < depth; ++lvl) {
-                    const uint16_t cc = s_cut[t * nin + node - 1];
-                    const int f = cc & 0xff;
-                    const int c = cc >> 8;
-                    const int code = s_x[f * XS + threadIdx.x];
-                    if (missing && code == kMissingCode) break;   // stops at this node
-                    node = 2 * node + (code >= c ? 1 : 0);
-                }
-                Fv += s_leaf[t * nleaf + node - first_id];
-            }
-        }
-        if (i < n) {
-            prob[i] = (float)(1.0 / (1.0 + exp(-2.0 * Fv)));
-            if (score) score[i] = Fv;
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
 // Forest traversal for depth <= 3.  Every thread scores four adjacent events,
 // one per byte of a word.  The 2^D - 1 cuts of a tree are uniform across the
 // workgroup, so they come as scalar loads of a per-tree record of 16 words:
@@ -2471,7 +2410,9 @@ __device__ __forceinline__ void stage_codes(uint8_t *s_x, int xs, int word,
 // decides bit l of the codes that start with p, missing ones are NaN; see
 // encode_kernel).  A value's code is the number of thresholds at or below
 // it.  NaN compares false with every threshold: code 0, the left branch of
-// every cut, as the threshold test gives.
+// every cut, as the threshold test gives; with missing (section 4.2) it takes
+// the missing code, which no count reaches (at most 254 thresholds then).
+template <bool MISSING>
 __device__ __forceinline__ void stage_values(uint8_t *s_x, int xs, int word,
                                              const uint32_t *s_tab, const float *__restrict__ xf,
                                              int64_t ldx, int64_t n, int64_t i0, int f0, int fstep,
@@ -2506,6 +2447,9 @@ __device__ __forceinline__ void stage_values(uint8_t *s_x, int xs, int word,
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
                         c[e] = 2u * c[e] + (thr[(1 << l) + c[e]] <= v[u][e] ? 1u : 0u);
+                if (MISSING)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) c[e] = v[u][e] != v[u][e] ? kMissingCode : c[e];
                 *reinterpret_cast<uint32_t *>(s_x + f * xs + 4 * word) =
                     c[0] | c[1] << 8 | c[2] << 16 | c[3] << 24;
             }
@@ -2571,7 +2515,7 @@ __global__ __launch_bounds__(1024) void apply_shallow_kernel(
         // barrier publishes the threshold table)
         if (FLOATS) {
             if (!staged) __syncthreads();
-            stage_values(s_x, XS, threadIdx.x, s_tab, xf, ldx, n, i0, 0, 1, d_used);
+            stage_values<false>(s_x, XS, threadIdx.x, s_tab, xf, ldx, n, i0, 0, 1, d_used);
         } else {
             stage_codes(s_x, XS, threadIdx.x, xb, ldb, n, i0, 0, 1, d_used);
         }
@@ -2652,7 +2596,7 @@ __global__ __launch_bounds__(kSplitThreads) void apply_split_kernel(
     if (FLOATS) {
         for (int q = threadIdx.x; q < ftab_words; q += kSplitThreads) s_tab[q] = ftab[q];
         __syncthreads();
-        stage_values(s_x, XS, lane, s_tab, xf, ldx, n, base + 4 * lane, wave, kWaves, d_used);
+        stage_values<false>(s_x, XS, lane, s_tab, xf, ldx, n, base + 4 * lane, wave, kWaves, d_used);
     } else {
         stage_codes(s_x, XS, lane, xb, ldb, n, base + 4 * lane, wave, kWaves, d_used);
     }
@@ -2694,6 +2638,205 @@ __global__ __launch_bounds__(kSplitThreads) void apply_split_kernel(
                 for (int u = 0; u < 8; ++u) F += l[u];
             }
             for (; q < tc; ++q) F += leaf_at(s_leaf + q * NLEAF, mine[q * kSplitEvents], 0);
+        }
+    }
+    const int64_t i = base + threadIdx.x;
+    if (threadIdx.x < kSplitEvents && i < n) {
+        prob[i] = (float)(1.0 / (1.0 + exp(-2.0 * F)));
+        if (score) score[i] = F;
+    }
+}
+
+// Traversal of deeper trees, and of trees with missing values (section 4.2),
+// four events per lane.  Without missing values the first three levels are
+// decided as in the shallow traversal (scalar records, byte carries); below
+// them, and with missing values from the root, each event follows its own
+// path: one record per node in LDS, feature * XS << 8 | bin, and one byte of
+// the event's code row per level, for U trees and four events (8 or more
+// independent chains) at once.  An event whose code of a node's cut feature
+// is missing stays at the node: at the levels that follow it meets the same
+// record and the same code.  Returns the reached slot of the tree's boost
+// weights in each byte: the leaf, or with missing values the node in heap
+// order (at most 254).
+template <bool MISSING, int U>
+__device__ __forceinline__ void deep_slot4(const uint8_t *xquad, const uint32_t *nodes, int t0,
+                                           const uint32_t *s_rec, int nin, int depth,
+                                           uint32_t (&m)[U]) {
+    uint32_t k[U][4];   // heap index of each event's node, from 0
+    int level = 0;
+    if (!MISSING) {     // (depth > 3)
+        NodeBatch<U> nb;
+        nb.load(nodes, t0);
+        uint32_t top[U];
+        shallow_leaf4<3, U>(xquad, nb, top);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) k[u][e] = 7u + ((top[u] >> (8 * e + 3)) & 7u);
+        level = 3;
+    } else {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) k[u][e] = 0u;
+    }
+    for (; level < depth; ++level) {
+        uint32_t rec[U][4], code[U][4];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) rec[u][e] = s_rec[u * nin + k[u][e]];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) code[u][e] = xquad[(rec[u][e] >> 8) + e];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t child =
+                    2u * k[u][e] + (code[u][e] >= (rec[u][e] & 0xffu) ? 2u : 1u);
+                k[u][e] = MISSING && code[u][e] == (uint32_t)kMissingCode ? k[u][e] : child;
+            }
+    }
+    const uint32_t first = MISSING ? 0u : (uint32_t)nin;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        m[u] = (k[u][0] - first) | (k[u][1] - first) << 8 | (k[u][2] - first) << 16 |
+               (k[u][3] - first) << 24;
+}
+
+// Stages the boost weights and node records of the trees [t0, t0 + tc).
+__device__ __forceinline__ void stage_trees(double *s_leaf, uint32_t *s_rec, const double *leaves,
+                                            const uint32_t *recs, int t0, int tc, int nval,
+                                            int nin) {
+    for (int q = threadIdx.x; q < tc * nval; q += blockDim.x)
+        s_leaf[q] = leaves[(size_t)t0 * nval + q];
+    for (int q = threadIdx.x; q < tc * nin; q += blockDim.x)
+        s_rec[q] = recs[(size_t)t0 * nin + q];
+}
+
+// Bulk traversal of deep trees: tiles, chunks of trees and launch shape as in
+// apply_shallow_kernel.  Bound by the per-event levels: two LDS reads (record,
+// code) and about six vector instructions each.  4M events of 40 features,
+// 100 trees of depth 6: 545 us, 1,110 us with one event per thread walking every
+// level; 2M events with a tenth of some features missing: 424 us, 580 us before.
+constexpr int kDeepBatch = 2;
+template <bool MISSING, bool FLOATS>
+__global__ __launch_bounds__(1024) void apply_deep_kernel(
+    const uint8_t *__restrict__ xb, int64_t ldb, const float *__restrict__ xf, int64_t ldx,
+    const uint32_t *__restrict__ ftab, int ftab_words, int64_t n, int d_used,
+    const uint32_t *__restrict__ nodes, const uint32_t *__restrict__ recs,
+    const double *__restrict__ leaves, int T, int depth, int tpc, double f0,
+    float *__restrict__ prob, double *__restrict__ score) {
+    extern __shared__ double smem[];
+    const int nin = (1 << depth) - 1, nval = MISSING ? 2 * nin + 1 : nin + 1;
+    double *s_leaf = smem;                                                        // [tpc][nval]
+    uint32_t *s_rec = reinterpret_cast<uint32_t *>(s_leaf + (size_t)tpc * nval);  // [tpc][nin]
+    uint8_t *s_x = reinterpret_cast<uint8_t *>(s_rec + (size_t)tpc * nin);        // [d_used][XS]
+    const int XS = 4 * blockDim.x;   // the stride the records were prepared for
+    uint32_t *s_tab = reinterpret_cast<uint32_t *>(s_x + (size_t)d_used * XS);    // FLOATS
+    if (FLOATS) {
+        for (int q = threadIdx.x; q < ftab_words; q += blockDim.x) s_tab[q] = ftab[q];
+    }
+    const int nchunks = (T + tpc - 1) / tpc;
+    const int64_t ntiles = (n + XS - 1) / XS;
+    const uint8_t *xquad = s_x + 4 * threadIdx.x;
+    bool staged = false;
+    for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+        const int64_t i0 = tile * XS + 4 * threadIdx.x;   // this thread's events
+        // (a thread stages and reads its own words of the tile only)
+        if (FLOATS) {
+            if (!staged) __syncthreads();
+            stage_values<MISSING>(s_x, XS, threadIdx.x, s_tab, xf, ldx, n, i0, 0, 1, d_used);
+        } else {
+            stage_codes(s_x, XS, threadIdx.x, xb, ldb, n, i0, 0, 1, d_used);
+        }
+        double F[4] = {f0, f0, f0, f0};
+        for (int ch = 0; ch < nchunks; ++ch) {
+            const int t0 = ch * tpc;
+            const int tc = min(tpc, T - t0);
+            if (nchunks > 1 || !staged) {
+                __syncthreads();   // the chunk before is done with
+                stage_trees(s_leaf, s_rec, leaves, recs, t0, tc, nval, nin);
+                staged = true;
+                __syncthreads();
+            }
+            // (events beyond n walk whatever their words hold: codes, in range)
+            int t = 0;
+            for (; t + kDeepBatch <= tc; t += kDeepBatch) {
+                uint32_t m[kDeepBatch];
+                deep_slot4<MISSING, kDeepBatch>(xquad, nodes, t0 + t, s_rec + t * nin, nin, depth,
+                                                m);
+#pragma unroll
+                for (int u = 0; u < kDeepBatch; ++u)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        F[e] += s_leaf[(t + u) * nval + ((m[u] >> (8 * e)) & 0xffu)];
+            }
+            for (; t < tc; ++t) {
+                uint32_t m[1];
+                deep_slot4<MISSING, 1>(xquad, nodes, t0 + t, s_rec + t * nin, nin, depth, m);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) F[e] += s_leaf[t * nval + ((m[0] >> (8 * e)) & 0xffu)];
+            }
+        }
+        store_scores(F, i0, n, prob, score);
+    }
+}
+
+// The deep traversal for few events (see apply_split_kernel).
+template <bool MISSING, bool FLOATS>
+__global__ __launch_bounds__(kSplitThreads) void apply_deep_split_kernel(
+    const uint8_t *__restrict__ xb, int64_t ldb, const float *__restrict__ xf, int64_t ldx,
+    const uint32_t *__restrict__ ftab, int ftab_words, int64_t n, int d_used,
+    const uint32_t *__restrict__ nodes, const uint32_t *__restrict__ recs,
+    const double *__restrict__ leaves, int T, int depth, int tpc, double f0,
+    float *__restrict__ prob, double *__restrict__ score) {
+    constexpr int XS = kSplitEvents;
+    constexpr int kWaves = kSplitThreads / kWave;
+    extern __shared__ double smem[];
+    const int nin = (1 << depth) - 1, nval = MISSING ? 2 * nin + 1 : nin + 1;
+    double *s_leaf = smem;                                                        // [tpc][nval]
+    uint32_t *s_rec = reinterpret_cast<uint32_t *>(s_leaf + (size_t)tpc * nval);  // [tpc][nin]
+    uint32_t *s_m = s_rec + (size_t)tpc * nin;                                    // [tpc][kWave]
+    uint8_t *s_x = reinterpret_cast<uint8_t *>(s_m + (size_t)tpc * kWave);        // [d_used][XS]
+    uint32_t *s_tab = reinterpret_cast<uint32_t *>(s_x + (size_t)d_used * XS);    // FLOATS
+    const int lane = threadIdx.x % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int64_t base = (int64_t)blockIdx.x * kSplitEvents;
+    if (FLOATS) {
+        for (int q = threadIdx.x; q < ftab_words; q += kSplitThreads) s_tab[q] = ftab[q];
+        __syncthreads();
+        stage_values<MISSING>(s_x, XS, lane, s_tab, xf, ldx, n, base + 4 * lane, wave, kWaves,
+                              d_used);
+    } else {
+        stage_codes(s_x, XS, lane, xb, ldb, n, base + 4 * lane, wave, kWaves, d_used);
+    }
+    double F = f0;
+    for (int t0 = 0; t0 < T; t0 += tpc) {
+        const int tc = min(tpc, T - t0);
+        if (t0 > 0) __syncthreads();   // the chunk before is summed
+        stage_trees(s_leaf, s_rec, leaves, recs, t0, tc, nval, nin);
+        __syncthreads();               // the trees (and the codes) are staged
+        const uint8_t *xquad = s_x + 4 * lane;
+        for (int t = wave; t < tc; t += kWaves) {
+            uint32_t m[1];
+            deep_slot4<MISSING, 1>(xquad, nodes, t0 + t, s_rec + t * nin, nin, depth, m);
+            s_m[t * kWave + lane] = m[0];
+        }
+        __syncthreads();
+        if (threadIdx.x < kSplitEvents) {
+            const uint8_t *mine = reinterpret_cast<const uint8_t *>(s_m) + threadIdx.x;
+            int q = 0;
+            for (; q + 8 <= tc; q += 8) {
+                double l[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) l[u] = s_leaf[(q + u) * nval + mine[(q + u) * kSplitEvents]];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) F += l[u];
+            }
+            for (; q < tc; ++q) F += s_leaf[q * nval + mine[q * kSplitEvents]];
         }
     }
     const int64_t i = base + threadIdx.x;
@@ -2754,70 +2897,6 @@ __global__ __launch_bounds__(256) void importance_kernel(
         if (i < n)
             for (int f = 0; f < d_out; ++f)
                 imp[(int64_t)f * ldi + i] = f < d_used ? s_acc[f * nt + threadIdx.x] : 0.0;
-    }
-}
-
-// Forest traversal of float32 events with value thresholds (section 2.2:
-// the cut "bin >= c" of feature j is the test x >= b_j,c, the c-th training
-// boundary, since a value's bin counts the boundaries at or below it), for
-// trees deeper than kApplyShallowDepth or with missing values.  A workgroup
-// stages a tile of one event per thread, feature-major, in LDS, and chunks
-// of the forest's records rec: [T][2^D - 1] pairs (feature, threshold bits);
-// each event walks its path.
-template <int D>
-__global__ __launch_bounds__(1024) void apply_float_kernel(
-    const float *__restrict__ x, int64_t ldx, int64_t n, int d_used,
-    const uint2 *__restrict__ rec, const double *__restrict__ leaves, int T, bool missing,
-    int tpc, double f0, float *__restrict__ prob, double *__restrict__ score) {
-    constexpr int NIN = (1 << D) - 1;
-    // boost weights per tree: the leaves, or with missing values every node
-    // in heap order (a NaN value stops its event at the node cutting on it)
-    const int NLEAF = missing ? 2 * NIN + 1 : 1 << D;
-    const int first_id = missing ? 1 : 1 << D;
-    extern __shared__ double smem[];
-    double *s_leaf = smem;                                                    // [tpc][NLEAF]
-    uint2 *s_rec = reinterpret_cast<uint2 *>(s_leaf + (size_t)tpc * NLEAF);   // [tpc][NIN]
-    float *s_x = reinterpret_cast<float *>(s_rec + (size_t)tpc * NIN);
-    const int XS = blockDim.x;   // [d_used][XS]
-    const int nchunks = (T + tpc - 1) / tpc;
-    const int64_t ntiles = (n + blockDim.x - 1) / blockDim.x;
-    const float *xme = s_x + threadIdx.x;
-    bool staged = false;
-    for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const int64_t i = tile * blockDim.x + threadIdx.x;
-        __syncthreads();
-        for (int f = 0; f < d_used; ++f) s_x[f * XS + threadIdx.x] = i < n ? x[(int64_t)f * ldx + i] : 0.0f;
-        double Fv = f0;
-        for (int ch = 0; ch < nchunks; ++ch) {
-            const int t0 = ch * tpc;
-            const int tc = min(tpc, T - t0);
-            if (nchunks > 1 || !staged) {
-                __syncthreads();
-                for (int q = threadIdx.x; q < tc * NLEAF; q += blockDim.x)
-                    s_leaf[q] = leaves[(size_t)t0 * NLEAF + q];
-                for (int q = threadIdx.x; q < tc * NIN; q += blockDim.x) {
-                    const uint2 r = rec[(size_t)t0 * NIN + q];
-                    s_rec[q] = make_uint2(r.x * (uint32_t)XS, r.y);   // row offset
-                }
-                staged = true;
-            }
-            __syncthreads();
-            for (int t = 0; t < tc; ++t) {
-                int node = 1;
-#pragma unroll
-                for (int lvl = 0; lvl < D; ++lvl) {
-                    const uint2 r = s_rec[t * NIN + node - 1];
-                    const float xv = xme[r.x];
-                    if (missing && xv != xv) break;   // NaN: stops at this node
-                    node = 2 * node + (xv >= __uint_as_float(r.y) ? 1 : 0);
-                }
-                Fv += s_leaf[t * NLEAF + node - first_id];
-            }
-        }
-        if (i < n) {
-            prob[i] = (float)(1.0 / (1.0 + exp(-2.0 * Fv)));
-            if (score) score[i] = Fv;
-        }
     }
 }
 
@@ -2992,7 +3071,7 @@ hipError_t allow_list_lds(size_t max_lds) {
 hipError_t prepare_kernels(size_t max_lds) {
     const hipError_t e[] = {allow_hist_lds<1>(max_lds), allow_hist_lds<2>(max_lds),
                             allow_hist_lds<4>(max_lds), allow_hist_lds<5>(max_lds),
-                            allow_hist_lds<8>(max_lds), allow_lds(apply_kernel, max_lds),
+                            allow_hist_lds<8>(max_lds),
                             allow_lds(leaf_kernel<false, 0>, max_lds),
                             allow_lds(leaf_kernel<true, 0>, max_lds),
                             allow_lds(leaf_kernel<true, 1>, max_lds),
@@ -3010,13 +3089,14 @@ hipError_t prepare_kernels(size_t max_lds) {
                             allow_lds(apply_split_kernel<1, true>, max_lds),
                             allow_lds(apply_split_kernel<2, true>, max_lds),
                             allow_lds(apply_split_kernel<3, true>, max_lds),
-                            allow_lds(apply_float_kernel<1>, max_lds),
-                            allow_lds(apply_float_kernel<2>, max_lds),
-                            allow_lds(apply_float_kernel<3>, max_lds),
-                            allow_lds(apply_float_kernel<4>, max_lds),
-                            allow_lds(apply_float_kernel<5>, max_lds),
-                            allow_lds(apply_float_kernel<6>, max_lds),
-                            allow_lds(apply_float_kernel<7>, max_lds),
+                            allow_lds(apply_deep_kernel<false, false>, max_lds),
+                            allow_lds(apply_deep_kernel<false, true>, max_lds),
+                            allow_lds(apply_deep_kernel<true, false>, max_lds),
+                            allow_lds(apply_deep_kernel<true, true>, max_lds),
+                            allow_lds(apply_deep_split_kernel<false, false>, max_lds),
+                            allow_lds(apply_deep_split_kernel<false, true>, max_lds),
+                            allow_lds(apply_deep_split_kernel<true, false>, max_lds),
+                            allow_lds(apply_deep_split_kernel<true, true>, max_lds),
                             allow_lds(importance_kernel, max_lds),
                             allow_lds(hist_reference_kernel, max_lds),
                             allow_list_lds<4>(max_lds), allow_list_lds<8>(max_lds),
@@ -3605,125 +3685,118 @@ hipError_t launch_route(const uint8_t *xb, int64_t ldb, int64_t n, int d, uint8_
 }
 
 ApplyShape plan_apply(int64_t n, int d_used, int n_trees, int depth, bool missing,
-                      int cu_count, size_t max_lds, int threads, size_t extra_lds) {
+                      int cu_count, size_t max_lds, int threads, size_t table_bytes) {
     ApplyShape as{};
     as.d_used = d_used;
     as.missing = missing;
-    // boost weights per tree: the leaves, or with missing values every node
-    const int nin = (1 << depth) - 1, nleaf = missing ? 2 * nin + 1 : 1 << depth;
-    const size_t lds_cap = max_lds > kHistStaticLdsReserve ? max_lds - kHistStaticLdsReserve : 0;
     as.shallow = depth <= kApplyShallowDepth && !missing;
-    const size_t leaf_bytes = (size_t)nleaf * 8;
-    if (as.shallow && threads <= 0 && n <= (int64_t)kSplitEvents * kSplitRounds * cu_count &&
-        (size_t)d_used * kSplitEvents + extra_lds + 64 + leaf_bytes + kWave * 4 <= lds_cap) {
+    // boost weights per tree: the leaves, or with missing values every node;
+    // the deep kernels also stage a record per node
+    const int nin = (1 << depth) - 1, nval = missing ? 2 * nin + 1 : nin + 1;
+    const int64_t per_tree = (int64_t)nval * 8 + (as.shallow ? 0 : (int64_t)nin * 4);
+    const int64_t extra = ((int64_t)table_bytes + 15) & ~(int64_t)15;   // float thresholds
+    const int64_t lds_cap = max_lds > kHistStaticLdsReserve ? max_lds - kHistStaticLdsReserve : 0;
+    const auto trees = [&](int64_t room, int64_t bytes) {
+        int64_t t = std::min<int64_t>(n_trees, room > 0 ? room / bytes : 0);
+        if (t < n_trees && t > kApplyBatch) t = t / kApplyBatch * kApplyBatch;
+        return (int)t;
+    };
+    const int64_t split_fixed = (int64_t)d_used * kSplitEvents + extra + 64;
+    if (threads <= 0 && n <= (int64_t)kSplitEvents * kSplitRounds * cu_count &&
+        trees(lds_cap - split_fixed, per_tree + kWave * 4) >= 1) {
         // few events: the wavefronts of a workgroup share the trees
         as.split = true;
         as.threads = kSplitThreads;
         as.node_stride = kSplitEvents;
-        const size_t xtile = (size_t)d_used * kSplitEvents + extra_lds;
-        int64_t tpc = (int64_t)((lds_cap - xtile - 64) / (leaf_bytes + kWave * 4));
-        if (tpc > n_trees) tpc = n_trees;
-        if (tpc < n_trees) tpc = tpc > kApplyBatch ? tpc / kApplyBatch * kApplyBatch : tpc;
-        as.trees_per_chunk = (int)tpc;
-        as.lds_bytes = (size_t)tpc * (leaf_bytes + kWave * 4) + xtile;
+        as.trees_per_chunk = trees(lds_cap - split_fixed, per_tree + kWave * 4);
+        as.lds_bytes = (size_t)(as.trees_per_chunk * (per_tree + kWave * 4) + split_fixed - 64);
         as.blocks = (int)((n + kSplitEvents - 1) / kSplitEvents);
         return as;
     }
-    if (as.shallow) {
-        // the workgroup size and workgroups per CU of least rounds x time.  A
-        // round of W wavefronts per CU takes about 6.5 + 0.75 W (W = 24 most,
-        // at least 12 in these units of 7 us for 400 trees): the traversal needs
-        // three or more wavefronts per SIMD to keep the vector units busy (10M
-        // events of 40 features: 1.58 ms with 8 per CU, 1.33 ms with 12; of 8
-        // features: 1.02 ms with 24, 1.07 ms with 32).  A workgroup holds its
-        // tile of codes and all leaf values, or at least 16 KiB of them at a time.
-        const int64_t all = (int64_t)n_trees * (int64_t)leaf_bytes;
-        const int64_t least = std::min<int64_t>(all, 16384);
-        double best = 0.0;
-        int best_t = 0, best_w = 1;
-        for (int w = 1; w <= 4; ++w)
-            for (int t = 256; t <= 1024 && w * t <= 24 * kWave; t += 256) {
-                const int64_t room = (int64_t)(max_lds / w) - (int64_t)kHistStaticLdsReserve -
-                                     64 - (int64_t)extra_lds - (int64_t)d_used * 4 * t;
-                if (room < least) continue;
-                const int64_t round = 4 * (int64_t)t * w * cu_count;
-                const double cost = (double)((n + round - 1) / round) *
-                                    std::max(12.0, 6.5 + 0.75 * (w * t / kWave));
-                if (best == 0.0 || cost < best) {
-                    best = cost;
-                    best_t = t;
-                    best_w = w;
-                }
+    // the workgroup size and workgroups per CU of least rounds x time.  A
+    // round of W wavefronts per CU takes about 6.5 + 0.75 W (W = 24 most, at
+    // least 12 in these units of 7 us for 400 trees of depth 3): the traversal
+    // needs three or more wavefronts per SIMD to keep the vector units busy (10M
+    // events of 40 features: 1.58 ms with 8 per CU, 1.33 ms with 12; of 8
+    // features: 1.02 ms with 24, 1.07 ms with 32).  A workgroup holds its
+    // tile of codes and all trees' weights (and records), or at least 16 KiB
+    // of them at a time.
+    const int64_t least = std::max(std::min<int64_t>(n_trees * per_tree, 16384), per_tree);
+    double best = 0.0;
+    int best_t = 0, best_w = 1;
+    for (int w = 1; w <= 4; ++w)
+        for (int t = 256; t <= 1024 && w * t <= 24 * kWave; t += 256) {
+            const int64_t room = (int64_t)(max_lds / w) - (int64_t)kHistStaticLdsReserve - 64 -
+                                 extra - (int64_t)d_used * 4 * t;
+            if (room < least) continue;
+            const int64_t round = 4 * (int64_t)t * w * cu_count;
+            const double cost = (double)((n + round - 1) / round) *
+                                std::max(12.0, 6.5 + 0.75 * (w * t / kWave));
+            if (best == 0.0 || cost < best) {
+                best = cost;
+                best_t = t;
+                best_w = w;
             }
-        int t = threads > 0 ? threads : best_t > 0 ? best_t : 256;
-        while (t > 64 && (size_t)d_used * 4 * t + leaf_bytes + extra_lds + 64 > lds_cap) t -= 64;
-        as.threads = t;
-        as.node_stride = 4 * t;
-        const size_t xtile = (size_t)d_used * 4 * t + extra_lds;
-        const size_t cap = best_t > 0 && threads <= 0 ? max_lds / best_w - kHistStaticLdsReserve
-                                                      : lds_cap;
-        const size_t room = cap > xtile + 64 ? cap - xtile - 64 : 0;
-        int64_t tpc = std::min<int64_t>(n_trees, (int64_t)(room / leaf_bytes));
-        if (tpc < n_trees) tpc = tpc / kApplyBatch * kApplyBatch;
-        if (tpc < 1) tpc = 1;
-        as.trees_per_chunk = (int)tpc;
-        as.lds_bytes = (size_t)tpc * leaf_bytes + xtile;
-        as.per_cu = threads > 0 ? 2 : best_w;
-    } else {
-        // 768 threads (512 for depth 4) measured best on 8M events x 40
-        // features: two workgroups per CU keep 24 wavefronts resident
-        // (fewer when the tile of codes would pass 96 KiB)
-        int t = threads > 0 ? threads : (depth == 4 ? 512 : 768);
-        while (t > 64 && (size_t)d_used * (t + 4) > 96 * 1024) t -= 64;
-        as.threads = t;
-        const size_t xtile = (size_t)d_used * (as.threads + 4);
-        const size_t per_tree = (size_t)nleaf * 8 + (size_t)nin * 2;
-        size_t budget = 65536;
-        if (budget < xtile + per_tree + 64) budget = lds_cap;
-        size_t room = budget > xtile + 64 ? budget - xtile - 64 : 0;
-        int64_t tpc = (int64_t)(room / per_tree);
-        if (tpc < 1) tpc = 1;
-        if (tpc > n_trees) tpc = n_trees;
-        as.trees_per_chunk = (int)tpc;
-        as.lds_bytes =
-            (size_t)tpc * nleaf * 8 + ((((size_t)tpc * nin) + 3) & ~(size_t)3) * 2 + xtile;
-    }
-    const int64_t tile_events = as.shallow ? 4 * (int64_t)as.threads : as.threads;
+        }
+    const bool planned = best_t > 0 && threads <= 0;
+    int t = threads > 0 ? threads : best_t > 0 ? best_t : 256;
+    while (t > 64 && (int64_t)d_used * 4 * t + per_tree + extra + 64 > lds_cap) t -= 64;
+    as.threads = t;
+    as.node_stride = 4 * t;
+    const int64_t xtile = (int64_t)d_used * 4 * t + extra;
+    const int64_t cap =
+        planned ? (int64_t)(max_lds / best_w) - (int64_t)kHistStaticLdsReserve : lds_cap;
+    as.trees_per_chunk = std::max(trees(cap - xtile - 64, per_tree), 1);
+    as.lds_bytes = (size_t)(as.trees_per_chunk * per_tree + xtile);
+    const int64_t tile_events = 4 * (int64_t)t;
     const int64_t ntiles = (n + tile_events - 1) / tile_events;
-    int64_t blocks = (int64_t)cu_count * (as.shallow ? as.per_cu : 8);
+    int64_t blocks = (int64_t)cu_count * (planned ? best_w : 2);
     if (blocks > ntiles) blocks = ntiles;
     if (blocks < 1) blocks = 1;
     as.blocks = (int)blocks;
     return as;
 }
 
-hipError_t launch_apply(const ApplyShape &as, const uint8_t *xb, int64_t ldb, int64_t n,
-                        const uint16_t *cuts, const uint32_t *nodes, const double *leaves,
-                        int n_trees, int depth, double f0, float *prob, double *score,
-                        hipStream_t s) {
-    if (as.shallow) {
-        if (!nodes) return hipErrorInvalidValue;
-#define FBDT_APPLY_S(DV)                                                                        \
+hipError_t launch_apply(const ApplyShape &as, const ApplyInput &in, const uint32_t *nodes,
+                        const uint32_t *recs, const double *leaves, int n_trees, int depth,
+                        double f0, float *prob, double *score, hipStream_t s) {
+    const bool floats = in.xf != nullptr;
+    const bool top = !as.missing && depth >= 3;   // scalar records of the first levels
+    if ((as.shallow || top) && !nodes) return hipErrorInvalidValue;
+    if ((!as.shallow && !recs) || (floats && !in.ftab)) return hipErrorInvalidValue;
+#define FBDT_APPLY_ARGS                                                                         \
+    in.xb, in.ldb, in.xf, in.ldx, in.ftab, in.ftab_words, in.n, as.d_used, nodes
+#define FBDT_APPLY_S(DV, FL)                                                                    \
     if (as.split)                                                                               \
-        apply_split_kernel<DV, false><<<as.blocks, as.threads, as.lds_bytes, s>>>(              \
-            xb, ldb, nullptr, 0, nullptr, 0, n, as.d_used, nodes, leaves, n_trees,              \
-            as.trees_per_chunk, f0, prob, score);                                               \
+        apply_split_kernel<DV, FL><<<as.blocks, as.threads, as.lds_bytes, s>>>(                 \
+            FBDT_APPLY_ARGS, leaves, n_trees, as.trees_per_chunk, f0, prob, score);             \
     else                                                                                        \
-        apply_shallow_kernel<DV, false><<<as.blocks, as.threads, as.lds_bytes, s>>>(            \
-            xb, ldb, nullptr, 0, nullptr, 0, n, as.d_used, nodes, leaves, n_trees,              \
-            as.trees_per_chunk, f0, prob, score)
-        switch (depth) {
-        case 1: FBDT_APPLY_S(1); break;
-        case 2: FBDT_APPLY_S(2); break;
-        case 3: FBDT_APPLY_S(3); break;
-        default: return hipErrorInvalidValue;
-        }
-#undef FBDT_APPLY_S
-        return hipGetLastError();
+        apply_shallow_kernel<DV, FL><<<as.blocks, as.threads, as.lds_bytes, s>>>(               \
+            FBDT_APPLY_ARGS, leaves, n_trees, as.trees_per_chunk, f0, prob, score)
+#define FBDT_APPLY_D(MI, FL)                                                                    \
+    if (as.split)                                                                               \
+        apply_deep_split_kernel<MI, FL><<<as.blocks, as.threads, as.lds_bytes, s>>>(            \
+            FBDT_APPLY_ARGS, recs, leaves, n_trees, depth, as.trees_per_chunk, f0, prob,        \
+            score);                                                                             \
+    else                                                                                        \
+        apply_deep_kernel<MI, FL><<<as.blocks, as.threads, as.lds_bytes, s>>>(                  \
+            FBDT_APPLY_ARGS, recs, leaves, n_trees, depth, as.trees_per_chunk, f0, prob, score)
+    switch ((as.shallow ? depth : as.missing ? 5 : 4) + (floats ? 8 : 0)) {
+    case 1: FBDT_APPLY_S(1, false); break;
+    case 2: FBDT_APPLY_S(2, false); break;
+    case 3: FBDT_APPLY_S(3, false); break;
+    case 4: FBDT_APPLY_D(false, false); break;
+    case 5: FBDT_APPLY_D(true, false); break;
+    case 9: FBDT_APPLY_S(1, true); break;
+    case 10: FBDT_APPLY_S(2, true); break;
+    case 11: FBDT_APPLY_S(3, true); break;
+    case 12: FBDT_APPLY_D(false, true); break;
+    case 13: FBDT_APPLY_D(true, true); break;
+    default: return hipErrorInvalidValue;
     }
-    apply_kernel<<<as.blocks, as.threads, as.lds_bytes, s>>>(xb, ldb, n, as.d_used, cuts, leaves,
-                                                            n_trees, depth, as.missing,
-                                                            as.trees_per_chunk, f0, prob, score);
+#undef FBDT_APPLY_S
+#undef FBDT_APPLY_D
+#undef FBDT_APPLY_ARGS
     return hipGetLastError();
 }
 
@@ -3762,84 +3835,6 @@ hipError_t launch_importance(const ApplyShape &as, const uint8_t *xb, int64_t ld
     importance_kernel<<<as.blocks, as.threads, as.lds_bytes, s>>>(
         xb, ldb, n, as.d_used, cuts, gains, n_trees, depth, as.missing, as.trees_per_chunk, imp,
         ldi, d_out);
-    return hipGetLastError();
-}
-
-ApplyShape plan_apply_float(int64_t n, int d_used, int n_trees, int depth, bool missing,
-                            int cu_count, size_t max_lds, int threads, size_t table_bytes) {
-    if (depth <= kApplyShallowDepth && !missing) {
-        // the binned shallow traversal, its tile staged from the values with
-        // the threshold table beside it in LDS
-        return plan_apply(n, d_used, n_trees, depth, false, cu_count, max_lds, threads,
-                          (table_bytes + 15) & ~(size_t)15);
-    }
-    ApplyShape as{};
-    as.d_used = d_used;
-    as.missing = missing;
-    as.shallow = false;
-    const int nin = (1 << depth) - 1, nleaf = missing ? 2 * nin + 1 : 1 << depth;
-    const size_t lds_cap = max_lds > kHistStaticLdsReserve ? max_lds - kHistStaticLdsReserve : 0;
-    // one event per thread, 768 threads (measured best on 8M events x 40
-    // features at depths 3 and 6): the tile of float32 values takes at most
-    // 124 KiB, the leaf values (and records) of as many trees as fit the rest
-    int t = threads > 0 ? threads : 768;
-    while (t > 64 && (size_t)d_used * t * 4 > 124 * 1024) t -= 64;
-    as.threads = t;
-    const size_t xtile = (size_t)d_used * t * 4;
-    const size_t per_tree = (size_t)nleaf * 8 + (size_t)nin * 8;
-    const size_t room = lds_cap > xtile + 64 ? lds_cap - xtile - 64 : 0;
-    int64_t tpc = (int64_t)(room / per_tree);
-    if (tpc < 1) tpc = 1;
-    if (tpc > n_trees) tpc = n_trees;
-    as.trees_per_chunk = (int)tpc;
-    as.lds_bytes = (size_t)tpc * per_tree + xtile;
-    const int64_t ntiles = (n + t - 1) / t;
-    int64_t blocks = (int64_t)cu_count * 4;
-    if (blocks > ntiles) blocks = ntiles;
-    if (blocks < 1) blocks = 1;
-    as.blocks = (int)blocks;
-    return as;
-}
-
-hipError_t launch_apply_float(const ApplyShape &as, const float *x, int64_t ldx, int64_t n,
-                              const uint2 *rec, const uint32_t *fnodes, const uint32_t *ftab,
-                              int ftab_words, const double *leaves, int n_trees, int depth,
-                              double f0, float *prob, double *score, hipStream_t s) {
-    if (as.shallow) {
-        if (!fnodes || !ftab) return hipErrorInvalidValue;
-#define FBDT_APPLY_FS(DV)                                                                       \
-    if (as.split)                                                                               \
-        apply_split_kernel<DV, true><<<as.blocks, as.threads, as.lds_bytes, s>>>(               \
-            nullptr, 0, x, ldx, ftab, ftab_words, n, as.d_used, fnodes, leaves, n_trees,        \
-            as.trees_per_chunk, f0, prob, score);                                               \
-    else                                                                                        \
-        apply_shallow_kernel<DV, true><<<as.blocks, as.threads, as.lds_bytes, s>>>(             \
-            nullptr, 0, x, ldx, ftab, ftab_words, n, as.d_used, fnodes, leaves, n_trees,        \
-            as.trees_per_chunk, f0, prob, score)
-        switch (depth) {
-        case 1: FBDT_APPLY_FS(1); break;
-        case 2: FBDT_APPLY_FS(2); break;
-        case 3: FBDT_APPLY_FS(3); break;
-        default: return hipErrorInvalidValue;
-        }
-#undef FBDT_APPLY_FS
-        return hipGetLastError();
-    }
-#define FBDT_APPLY_F(DV)                                                                        \
-    apply_float_kernel<DV><<<as.blocks, as.threads, as.lds_bytes, s>>>(                         \
-        x, ldx, n, as.d_used, rec, leaves, n_trees, as.missing, as.trees_per_chunk, f0, prob,  \
-        score)
-    switch (depth) {
-    case 1: FBDT_APPLY_F(1); break;
-    case 2: FBDT_APPLY_F(2); break;
-    case 3: FBDT_APPLY_F(3); break;
-    case 4: FBDT_APPLY_F(4); break;
-    case 5: FBDT_APPLY_F(5); break;
-    case 6: FBDT_APPLY_F(6); break;
-    case 7: FBDT_APPLY_F(7); break;
-    default: return hipErrorInvalidValue;
-    }
-#undef FBDT_APPLY_F
     return hipGetLastError();
 }
 

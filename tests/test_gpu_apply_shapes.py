@@ -47,6 +47,40 @@ def test_shallow_apply(n, d, B, D, T):
     assert np.allclose(got.cpu().numpy(), p, rtol=0, atol=6e-8)
 
 
+@pytest.mark.parametrize("n,d,B,D,T,missing", [
+    (1, 1, 2, 4, 1, False), (259, 40, 256, 6, 17, False), (1000, 255, 256, 7, 40, False),
+    (393_217, 9, 256, 4, 5, False), (400_003, 40, 64, 7, 60, False), (450_001, 255, 256, 5, 3, False),
+    (1, 1, 2, 1, 1, True), (257, 12, 255, 3, 9, True), (1023, 40, 100, 7, 33, True),
+    (393_219, 7, 255, 2, 4, True), (400_001, 60, 200, 6, 30, True),
+])
+def test_deep_and_missing_apply(n, d, B, D, T, missing):
+    rng = np.random.default_rng([n, d, T])
+    f = random_forest(T, D, d, B, n + T)
+    xb = rng.integers(0, B, (d, n)).astype(np.uint8)
+    inner = None
+    if missing:
+        inner = rng.normal(0.0, 0.05, f["cut_bin"].shape)
+        xb[rng.random((d, n)) < 0.2] = 255
+    om = O.Model(D, B, d, f["f0"], f["cut_feature"], f["cut_bin"], np.zeros_like(f["leaf"]),
+                 f["leaf"], inner)
+    p, F = O.apply(om, xb)
+    bounds = np.repeat(np.arange(1, B, dtype=np.float32)[None], d, axis=0)
+    m = fb.Model.from_arrays(f["cut_feature"], f["cut_bin"], f["leaf"], f["f0"], d, B,
+                             boundaries=bounds, inner=inner)
+    score = torch.empty(n, dtype=torch.float64, device="cuda")
+    got = fb.apply(m, fb.Codes.from_numpy(xb), score=score)
+    assert np.array_equal(score.cpu().numpy(), F)
+    assert np.allclose(got.cpu().numpy(), p, rtol=0, atol=6e-8)
+    x = xb.astype(np.float32) + 0.5
+    if missing:
+        x[xb == 255] = np.nan
+    wide = torch.zeros(d, n + 5, device="cuda")[:, 1:n + 1]
+    wide.copy_(torch.from_numpy(x))
+    score.zero_()
+    fb.apply_float(m, wide, score=score)
+    assert np.array_equal(score.cpu().numpy(), F)
+
+
 def test_calls_of_few_and_many_events_interleave():
     """Both kernels' node records stay in place for launches still queued."""
     d, B, D, T = 40, 256, 3, 400
