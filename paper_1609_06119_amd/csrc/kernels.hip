@@ -21,6 +21,7 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstdint>
+#include <type_traits>
 
 namespace fbdt {
 namespace {
@@ -2850,49 +2851,97 @@ __global__ __launch_bounds__(kSplitThreads) void apply_deep_split_kernel(
 // an event's path adds its separation gain to the importance of the node's
 // cut feature, tree by tree in float64.  A workgroup stages a tile of codes
 // (one event per thread) and chunks of the forest (packed cut and gain) in
-// LDS; each thread keeps its event's accumulators in an LDS column.
-__global__ __launch_bounds__(256) void importance_kernel(
+// LDS; each thread keeps its event's accumulators in an LDS column.  The paths
+// through U trees are walked together, then their gains are added tree by
+// tree, level by level, with non-returning LDS adds: a column has one
+// writer, whose LDS operations complete in order, so the sums are those of
+// adding one after another, and no add waits for the one before.  The
+// accumulators (8 bytes per event and feature) leave 6 wavefronts per CU for
+// 40 features: bound by the walk's dependent reads at that occupancy.  500,000
+// events of 40 features, 200 trees of depth 3: 232 us (one tree at a time
+// with loaded and stored accumulators: 966 us).
+template <int D, bool MISSING>
+__global__ __launch_bounds__(1024) void importance_kernel(
     const uint8_t *__restrict__ xb, int64_t ldb, int64_t n, int d_used,
-    const uint16_t *__restrict__ cuts, const double *__restrict__ gains, int T, int depth,
-    bool missing, int tpc, double *__restrict__ imp, int64_t ldi, int d_out) {
+    const uint16_t *__restrict__ cuts, const double *__restrict__ gains, int T, int tpc,
+    double *__restrict__ imp, int64_t ldi, int d_out) {
+    constexpr int NIN = (1 << D) - 1;
+    constexpr int U = D <= 3 ? 4 : 2;
     extern __shared__ double smem[];
-    const int nin = (1 << depth) - 1;
-    const int nt = blockDim.x;
-    double *s_gain = smem;                            // [tpc][nin]
-    double *s_acc = s_gain + (size_t)tpc * nin;       // [d_used][nt]
-    uint16_t *s_cut = reinterpret_cast<uint16_t *>(s_acc + (size_t)d_used * nt);   // [tpc][nin]
-    uint8_t *s_x = reinterpret_cast<uint8_t *>(s_cut + (((size_t)tpc * nin + 3) & ~(size_t)3));
-    const int XS = nt + 4;
+    const uint32_t nt = blockDim.x;
+    double *s_gain = smem;                            // [tpc][NIN]
+    double *s_acc = s_gain + (size_t)tpc * NIN;       // [d_used][nt]
+    uint16_t *s_cut = reinterpret_cast<uint16_t *>(s_acc + (size_t)d_used * nt);   // [tpc][NIN]
+    uint8_t *s_x = reinterpret_cast<uint8_t *>(s_cut + (((size_t)tpc * NIN + 3) & ~(size_t)3));
     const int nchunks = (T + tpc - 1) / tpc;
     const int64_t ntiles = (n + nt - 1) / nt;
+    bool staged = false;
+    // the path of this thread's event through trees t .. t + W - 1
+    const auto walk = [&](auto width, int t) {
+        constexpr int W = decltype(width)::value;
+        uint32_t at[W][D];
+        double g[W][D];
+        uint32_t k[W];
+#pragma unroll
+        for (int u = 0; u < W; ++u) k[u] = 0u;
+#pragma unroll
+        for (int l = 0; l < D; ++l) {
+            uint32_t cut[W], code[W];
+#pragma unroll
+            for (int u = 0; u < W; ++u) {
+                const uint32_t q = (uint32_t)(t + u) * NIN + k[u];
+                cut[u] = s_cut[q];
+                g[u][l] = s_gain[q];
+            }
+#pragma unroll
+            for (int u = 0; u < W; ++u) {
+                at[u][l] = __umul24(cut[u] & 0xffu, nt) + threadIdx.x;
+                code[u] = s_x[at[u][l]];
+            }
+#pragma unroll
+            for (int u = 0; u < W; ++u) {
+                const uint32_t child = 2u * k[u] + (code[u] >= (cut[u] >> 8) ? 2u : 1u);
+                if (MISSING && code[u] == (uint32_t)kMissingCode)
+                    g[u][l] = 0.0;   // the cut does not apply: the event stays here
+                else
+                    k[u] = child;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < W; ++u)
+#pragma unroll
+            for (int l = 0; l < D; ++l) unsafeAtomicAdd(s_acc + at[u][l], g[u][l]);
+    };
     for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
         const int64_t i = tile * nt + threadIdx.x;
-        __syncthreads();
-        for (int f = 0; f < d_used; ++f) {
-            s_x[f * XS + threadIdx.x] = i < n ? xb[(int64_t)f * ldb + i] : 0;
-            s_acc[f * nt + threadIdx.x] = 0.0;
+        // (a thread uses its own column and bytes of the tile only)
+        for (int f0 = 0; f0 < d_used; f0 += 8) {
+            uint8_t v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                v[u] = i < n ? xb[(int64_t)min(f0 + u, d_used - 1) * ldb + i] : 0;
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (f0 + u < d_used) {
+                    s_x[(f0 + u) * nt + threadIdx.x] = v[u];
+                    s_acc[(f0 + u) * nt + threadIdx.x] = 0.0;
+                }
         }
         for (int ch = 0; ch < nchunks; ++ch) {
             const int t0 = ch * tpc;
             const int tc = min(tpc, T - t0);
-            __syncthreads();
-            for (int q = threadIdx.x; q < tc * nin; q += nt) {
-                s_gain[q] = gains[(size_t)t0 * nin + q];
-                s_cut[q] = cuts[(size_t)t0 * nin + q];
-            }
-            __syncthreads();
-            for (int t = 0; t < tc; ++t) {
-                int node = 1;
-                for (int lvl = 0; lvl < depth; ++lvl) {
-                    const int k = t * nin + node - 1;
-                    const uint16_t cc = s_cut[k];
-                    const int f = cc & 0xff;
-                    const int code = s_x[f * XS + threadIdx.x];
-                    if (missing && code == kMissingCode) break;   // the cut does not apply
-                    s_acc[f * nt + threadIdx.x] += s_gain[k];
-                    node = 2 * node + (code >= (cc >> 8) ? 1 : 0);
+            if (nchunks > 1 || !staged) {
+                __syncthreads();
+                for (int q = threadIdx.x; q < tc * NIN; q += nt) {
+                    s_gain[q] = gains[(size_t)t0 * NIN + q];
+                    s_cut[q] = cuts[(size_t)t0 * NIN + q];
                 }
+                staged = true;
+                __syncthreads();
             }
+            int t = 0;
+            for (; t + U <= tc; t += U) walk(std::integral_constant<int, U>{}, t);
+            for (; t < tc; ++t) walk(std::integral_constant<int, 1>{}, t);
         }
         if (i < n)
             for (int f = 0; f < d_out; ++f)
@@ -3097,7 +3146,20 @@ hipError_t prepare_kernels(size_t max_lds) {
                             allow_lds(apply_deep_split_kernel<false, true>, max_lds),
                             allow_lds(apply_deep_split_kernel<true, false>, max_lds),
                             allow_lds(apply_deep_split_kernel<true, true>, max_lds),
-                            allow_lds(importance_kernel, max_lds),
+                            allow_lds(importance_kernel<1, false>, max_lds),
+                            allow_lds(importance_kernel<1, true>, max_lds),
+                            allow_lds(importance_kernel<2, false>, max_lds),
+                            allow_lds(importance_kernel<2, true>, max_lds),
+                            allow_lds(importance_kernel<3, false>, max_lds),
+                            allow_lds(importance_kernel<3, true>, max_lds),
+                            allow_lds(importance_kernel<4, false>, max_lds),
+                            allow_lds(importance_kernel<4, true>, max_lds),
+                            allow_lds(importance_kernel<5, false>, max_lds),
+                            allow_lds(importance_kernel<5, true>, max_lds),
+                            allow_lds(importance_kernel<6, false>, max_lds),
+                            allow_lds(importance_kernel<6, true>, max_lds),
+                            allow_lds(importance_kernel<7, false>, max_lds),
+                            allow_lds(importance_kernel<7, true>, max_lds),
                             allow_lds(hist_reference_kernel, max_lds),
                             allow_list_lds<4>(max_lds), allow_list_lds<8>(max_lds),
                             allow_list_lds<12>(max_lds), allow_list_lds<20>(max_lds),
@@ -3807,22 +3869,27 @@ ApplyShape plan_importance(int64_t n, int d_used, int n_trees, int depth, bool m
     as.missing = missing;
     const int nin = (1 << depth) - 1;
     const size_t lds_cap = max_lds > kHistStaticLdsReserve ? max_lds - kHistStaticLdsReserve : 0;
-    // one event per thread: its float64 accumulator column and code column
-    // take at most 96 KiB over the workgroup, the forest chunk the rest
-    int t = 256;
-    while (t > 64 && (size_t)d_used * ((size_t)t * 8 + t + 4) > 96 * 1024) t -= 64;
+    // one event per thread: its float64 accumulators and codes, and all trees'
+    // cuts and gains or at least 8 KiB of them, as many threads as fit; few
+    // events spread over the CUs
+    const int64_t per_tree = (int64_t)nin * 10;
+    const int64_t least = std::max(std::min<int64_t>(n_trees * per_tree, 8192), per_tree) + 64;
+    int t = 1024;
+    while (t > 64 && (int64_t)d_used * 9 * t + least > (int64_t)lds_cap) t -= 64;
+    const int64_t spread = ((n + cu_count - 1) / cu_count + 63) / 64 * 64;
+    if (spread < t) t = (int)spread;
     as.threads = t;
-    const size_t fixed = (size_t)d_used * ((size_t)t * 8 + t + 4) + 64;
-    const size_t per_tree = (size_t)nin * 10;
-    const size_t room = lds_cap > fixed ? lds_cap - fixed : 0;
-    int64_t tpc = (int64_t)(room / per_tree);
+    const int64_t fixed = (int64_t)d_used * 9 * t + 64;
+    const int64_t room = (int64_t)lds_cap > fixed ? (int64_t)lds_cap - fixed : 0;
+    int64_t tpc = std::min<int64_t>(room / per_tree, n_trees);
     if (tpc < 1) tpc = 1;
-    if (tpc > n_trees) tpc = n_trees;
     as.trees_per_chunk = (int)tpc;
     as.lds_bytes = (size_t)tpc * nin * 8 + (size_t)d_used * t * 8 +
-                   ((((size_t)tpc * nin) + 3) & ~(size_t)3) * 2 + (size_t)d_used * (t + 4);
+                   ((((size_t)tpc * nin) + 3) & ~(size_t)3) * 2 + (size_t)d_used * t;
     const int64_t ntiles = (n + t - 1) / t;
-    int64_t blocks = (int64_t)cu_count * 4;
+    int64_t per_cu = std::min<int64_t>((int64_t)max_lds / (int64_t)as.lds_bytes, 2048 / t);
+    if (per_cu < 1) per_cu = 1;
+    int64_t blocks = (int64_t)cu_count * per_cu;
     if (blocks > ntiles) blocks = ntiles;
     if (blocks < 1) blocks = 1;
     as.blocks = (int)blocks;
@@ -3832,9 +3899,24 @@ ApplyShape plan_importance(int64_t n, int d_used, int n_trees, int depth, bool m
 hipError_t launch_importance(const ApplyShape &as, const uint8_t *xb, int64_t ldb, int64_t n,
                              const uint16_t *cuts, const double *gains, int n_trees, int depth,
                              double *imp, int64_t ldi, int d_out, hipStream_t s) {
-    importance_kernel<<<as.blocks, as.threads, as.lds_bytes, s>>>(
-        xb, ldb, n, as.d_used, cuts, gains, n_trees, depth, as.missing, as.trees_per_chunk, imp,
-        ldi, d_out);
+#define FBDT_IMP(DV)                                                                            \
+    if (as.missing)                                                                             \
+        importance_kernel<DV, true><<<as.blocks, as.threads, as.lds_bytes, s>>>(                \
+            xb, ldb, n, as.d_used, cuts, gains, n_trees, as.trees_per_chunk, imp, ldi, d_out);  \
+    else                                                                                        \
+        importance_kernel<DV, false><<<as.blocks, as.threads, as.lds_bytes, s>>>(               \
+            xb, ldb, n, as.d_used, cuts, gains, n_trees, as.trees_per_chunk, imp, ldi, d_out)
+    switch (depth) {
+    case 1: FBDT_IMP(1); break;
+    case 2: FBDT_IMP(2); break;
+    case 3: FBDT_IMP(3); break;
+    case 4: FBDT_IMP(4); break;
+    case 5: FBDT_IMP(5); break;
+    case 6: FBDT_IMP(6); break;
+    case 7: FBDT_IMP(7); break;
+    default: return hipErrorInvalidValue;
+    }
+#undef FBDT_IMP
     return hipGetLastError();
 }
 

@@ -96,3 +96,23 @@ def test_calls_of_few_and_many_events_interleave():
     for a, b in runs:
         assert torch.equal(a, p_big) and torch.equal(b, p_few)
     assert torch.equal(p_few, p_big[:500])
+
+
+@pytest.mark.parametrize("n,d,B,D,T,missing", [
+    (1, 1, 2, 1, 1, False), (65, 40, 256, 3, 7, False), (100_001, 40, 256, 3, 230, False),
+    (5_003, 255, 256, 5, 40, False), (20_011, 9, 200, 7, 33, True), (70_001, 3, 255, 2, 9, True),
+])
+def test_event_importance(n, d, B, D, T, missing):
+    rng = np.random.default_rng([n, d, T, 1])
+    f = random_forest(T, D, d, B, n + T)
+    gain = rng.exponential(1.0, f["cut_bin"].shape)
+    xb = rng.integers(0, B, (d, n)).astype(np.uint8)
+    inner = None
+    if missing:
+        inner = rng.normal(0.0, 0.05, f["cut_bin"].shape)
+        xb[rng.random((d, n)) < 0.2] = 255
+    om = O.Model(D, B, d, f["f0"], f["cut_feature"], f["cut_bin"], gain, f["leaf"], inner)
+    m = fb.Model.from_arrays(f["cut_feature"], f["cut_bin"], f["leaf"], f["f0"], d, B, gain=gain,
+                             inner=inner)
+    got = fb.event_importance(m, fb.Codes.from_numpy(xb)).cpu().numpy()
+    assert np.array_equal(got, O.event_importance(om, xb))
