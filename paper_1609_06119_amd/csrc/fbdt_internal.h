@@ -115,7 +115,8 @@ constexpr int kXcdQuantum = 64;     // XCD event ranges are whole multiples of t
 // so that the per-event arrays one pass writes stay in that XCD's L2 for the
 // next pass: R = ceil(n / 8) rounded up to kXcdQuantum.
 int64_t xcd_range(int64_t n);
-constexpr int kValidateBlocks = 256;
+constexpr int kValidateBlocks = 512;
+constexpr int kAbsSumBlocks = 256;
 // LDS kept aside for a kernel's static shared arrays when sizing its
 // dynamic LDS (the histogram kernel's cut table takes 128 bytes)
 constexpr size_t kHistStaticLdsReserve = 1024;
@@ -137,8 +138,20 @@ hipError_t prepare_kernels(size_t max_lds);
 
 hipError_t launch_fill_u32(void *p, uint32_t value, size_t count, hipStream_t s);
 
-hipError_t launch_validate(const int8_t *y, const float *v, int64_t n, double *class_partial,
-                           int *err, hipStream_t s);
+// Zeroes up to kClearMost ranges of words in one launch.
+constexpr int kClearMost = 8;
+struct ClearList {
+    int count;
+    uint32_t *at[kClearMost];
+    size_t words[kClearMost];
+};
+hipError_t launch_clear(const ClearList &c, hipStream_t s);
+
+// Label and weight checks and the class totals; with v also v_out [npad] (v,
+// 0 beyond n) and sign_out [npad] (1 where v < 0), both 16-byte aligned, npad
+// a multiple of 4.
+hipError_t launch_validate(const int8_t *y, const float *v, int64_t n, int64_t npad, float *v_out,
+                           uint8_t *sign_out, double *class_partial, int *err, hipStream_t s);
 // err |= flag if any of the first n codes of a row equals `code`.
 hipError_t launch_find_code(const uint8_t *xb, int64_t ldb, int64_t n, int d, uint8_t code,
                             int flag, int *err, hipStream_t s);
@@ -235,14 +248,11 @@ hipError_t launch_hist_reference(int kind, const HistShape &hs, const uint8_t *x
                                  int64_t n, int d, const uint8_t *node, const float *w,
                                  uint32_t *sink, hipStream_t s);
 
-// vs[i] = 1 where v[i] < 0 (i < n), else 0, for i < npad.
-hipError_t launch_sign_bytes(const float *v, int64_t n, int64_t npad, uint8_t *vs, hipStream_t s);
-
 // hist[i] = (sum over chunks of partial[chunk][i]) * 2^-scale + small[i].
 hipError_t launch_merge_partials(const uint64_t *partial, int chunks, size_t count, int scale,
                                  const double *small, double *out, hipStream_t s);
 
-// Sum of |w| over n weights into *out (fixed order).
+// Sum of |w| over n weights into *out (fixed order); block_partial: [kAbsSumBlocks].
 hipError_t launch_abs_sum(const float *w, int64_t n, double *block_partial, double *out,
                           hipStream_t s);
 
