@@ -668,7 +668,7 @@ int fbdt_fit(const uint8_t *xb, int64_t n, int32_t d, int64_t ldb, int32_t n_bin
     for (int mode = 0; mode < (may_miss ? 2 : 1); ++mode) {
         std::vector<HistShape> &pl = mode == 0 ? plans_sib : plans_both;
         for (int l = 0; l < D; ++l) {
-            pl[l] = plan_histogram(n, d, n_bins, l, mode == 0, di.cu_count, di.max_lds,
+            pl[l] = plan_histogram(n, d, n_bins, l, true, mode == 0, di.cu_count, di.max_lds,
                                    hist_overrides());
             pl[l].prefix = true;   // the cut scan reads prefix-summed rows
             const size_t hnodes = pl[l].sibling ? (size_t)1 << (l - 1) : (size_t)1 << l;
@@ -1458,7 +1458,7 @@ int fbdt_histogram(const uint8_t *xb, int64_t n, int32_t d, int64_t ldb, int32_t
     DeviceInfo di;
     if ((rc = current_device(&dev, &di))) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    HistShape hs = plan_histogram(n, d, n_bins, layer, false, di.cu_count, di.max_lds,
+    HistShape hs = plan_histogram(n, d, n_bins, layer, false, false, di.cu_count, di.max_lds,
                                   hist_overrides());
     if (hs.lds_bytes + kHistStaticLdsReserve > di.max_lds)
         return fail(FBDT_E_INVAL, "layer %d needs %zu bytes of LDS, the device has %zu", layer,
@@ -1566,7 +1566,7 @@ int fbdt_reference_pass(int32_t kind, const uint8_t *xb, int64_t n, int32_t d, i
     DeviceInfo di;
     if ((rc = current_device(&dev, &di))) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const HistShape hs = plan_histogram(n, d, n_bins, layer, true, di.cu_count, di.max_lds,
+    const HistShape hs = plan_histogram(n, d, n_bins, layer, true, true, di.cu_count, di.max_lds,
                                         hist_overrides());
     Arena &a = g_arena[dev];
     std::lock_guard<std::mutex> lk(a.mu);

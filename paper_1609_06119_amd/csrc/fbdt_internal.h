@@ -177,10 +177,11 @@ hipError_t launch_tree_prep(const int8_t *y, const float *v, double *F, const do
                             double alpha, float *w, double *yts, double *score_out, int cu_count,
                             hipStream_t s);
 
-// ov: launch-shape overrides (0 = the planner's choice).  sibling: the
-// routed fit pass, which for layer >= 1 histograms one child per parent.
-HistShape plan_histogram(int64_t n, int d, int n_bins, int layer, bool sibling, int cu_count,
-                         size_t max_lds, const HistOverrides &ov);
+// ov: launch-shape overrides (0 = the planner's choice).  routed: a pass of a
+// fit (which routes layers of at most kRoutedMaxParents parents itself).
+// sibling: for layer >= 1 it histograms one child per parent.
+HistShape plan_histogram(int64_t n, int d, int n_bins, int layer, bool routed, bool sibling,
+                         int cu_count, size_t max_lds, const HistOverrides &ov);
 
 // Best-cut keys of a layer's nodes: the cut scan takes the maximum of every
 // candidate's 64-bit key (gain order, then lowest feature and bin) into

@@ -3272,8 +3272,8 @@ bool hist_fpg_supported(int f) {
     return false;
 }
 
-HistShape plan_histogram(int64_t n, int d, int n_bins, int layer, bool sibling, int cu_count,
-                         size_t max_lds, const HistOverrides &ov) {
+HistShape plan_histogram(int64_t n, int d, int n_bins, int layer, bool routed, bool sibling,
+                         int cu_count, size_t max_lds, const HistOverrides &ov) {
     const int fpg = ov.fpg, chunks = ov.chunks, threads = ov.threads;
     HistShape hs{};
     const int nodes = sibling && layer >= 1 ? 1 << (layer - 1) : 1 << layer;
@@ -3287,18 +3287,20 @@ HistShape plan_histogram(int64_t n, int d, int n_bins, int layer, bool sibling, 
     hs.nodes_per_group = npg;
     hs.node_groups = (nodes + npg - 1) / npg;
     // Features per workgroup f (one of kHistFpgSizes) and event chunks per
-    // XCD c8, from a cost model fitted to launches of this kernel on MI355X
-    // (0.5M-10M events, 20-40 features, 1-16 histogrammed nodes).  The pass
-    // is bound by LDS atomic issue: a ds_add_u64 wavefront instruction costs
-    // ~9 clocks whether half or all of its lanes are active, so a workgroup
-    // pays about kCostAdd us per thousand (event, feature) slots it streams,
-    // sampled or not, counted or not, plus kCostEvent per thousand events;
-    // the launch pays that once per round of workgroups, and every MB of
-    // chunk partials written (and summed again by the cut scan) costs about
-    // kCostPartial us.  With the CUs filled the slots per workgroup are about
-    // equal for every f, so the model takes the fewest chunks (fewest
-    // partials) that still fill the CUs, and it avoids node groups, which
-    // stream every event once per group.
+    // XCD c8, from a cost model fitted to 2,000 launches (and their cut scans)
+    // of this kernel on MI355X, by least squares and then by what its choices lose (0.05M-4M events, 12-60
+    // features, 64-256 bins, every layer of depth 4-6, with and without missing
+    // values): a workgroup pays per thousand events (its weights, ids and
+    // routing rows read and decoded: kEvent us by the way the layer is routed)
+    // and per thousand (event, feature) slots (kSlot: the LDS atomics), and for
+    // every LDS row it scans and writes (kRowCost); the launch pays that once per
+    // round of workgroups, and the chunk partials (written here, summed again
+    // by the cut scan) cost kPartial us per MB.  A layer that routes through
+    // the rows of four parents pays five times a feature's atomics per event,
+    // so it takes more features per workgroup than the root.  (With one cost
+    // per event for all layers, fitted to 20 and 40 features: 1M x 27, depth 6,
+    // layer 3 49.5 us with its cut scan against 28.7; 333k x 27 with missing
+    // values, layers 1-3 20.9, 27.8 and 31.5 us against 17.6, 20.6 and 25.1.)
     const int t_threads = threads > 0 ? threads : 1024;
     const int64_t min_events = (int64_t)kHistE * t_threads;
     const int64_t R = xcd_range(n);
@@ -3308,7 +3310,13 @@ HistShape plan_histogram(int64_t n, int d, int n_bins, int layer, bool sibling, 
     if (fpg > 0) {
         f = fpg;
     } else {
-        constexpr double kCostEvent = 0.01, kCostAdd = 0.057, kCostPartial = 0.25;
+        constexpr double kSlot = 0.042, kPartial = 0.45, kRowCost = 0.13, kMiss = 0.029;
+        const int parents = layer >= 1 ? 1 << (layer - 1) : 0;
+        double per_event = 0.100;   // ids of the layer itself
+        if (routed && parents <= kRoutedMaxParents) {
+            per_event = parents == 0 ? 0.089 : parents == 1 ? 0.095 : parents == 2 ? 0.176 : 0.222;
+            if (layer >= 1 && !sibling) per_event += kMiss;   // events may stop
+        }
         double best = 0.0;
         for (int cand : kHistFpgSizes) {
             if (cand > d && cand != kHistFpgSizes[0]) continue;
@@ -3324,7 +3332,8 @@ HistShape plan_histogram(int64_t n, int d, int n_bins, int layer, bool sibling, 
                 const int64_t wgs = kXcds * c8 * g;
                 const double rounds = (double)((wgs + cu_count - 1) / cu_count);
                 const double pmb = (double)(kXcds * c8) * nodes * d * n_bins * 16.0 / 1e6;
-                const double t = rounds * ek * (kCostEvent + kCostAdd * cand) + kCostPartial * pmb;
+                const double t = rounds * (ek * (per_event + kSlot * cand) + kRowCost * np * cand) +
+                                 kPartial * pmb;
                 if (c8_pick == 0 || t < best) {
                     best = t;
                     f = cand;
