@@ -44,7 +44,7 @@ struct fbdt_model {
         struct Records {
             int stride;
             uint32_t *nodes;   // [T][16] (depth <= 3, or the first three levels)
-            uint32_t *recs;    // [T][2^D - 1] (deep kernels)
+            uint32_t *recs;    // [T][2^D - 1] (deep kernels), in nodes' allocation
         } rec[2][2];
     };
     std::mutex mu;
@@ -400,26 +400,20 @@ int make_records(const fbdt_model *m, const ApplyShape &as, const Cut &cut,
     const uint32_t xs = (uint32_t)apply_node_stride(as);
     if (r.stride == (int)xs) return FBDT_OK;
     const size_t T = m->n_trees, nin = ((size_t)1 << m->depth) - 1;
-    if (as.shallow || !m->missing) {
-        const size_t top = std::min<size_t>(nin, 7);
-        std::vector<uint32_t> table(T * 16, 0u);
-        for (size_t t = 0; t < T; ++t)
-            for (size_t k = 0; k < top; ++k) {
-                const size_t q = t * nin + k;
-                table[t * 16 + k] = (uint32_t)m->cut_feature[q] * xs;
-                table[t * 16 + 8 + k] = (256u - cut(q)) * 0x01010101u;
-            }
-        if (!r.nodes)
-            HIP_TRY(device_alloc(reinterpret_cast<void **>(&r.nodes), table.size() * 4));
-        HIP_TRY(hipMemcpy(r.nodes, table.data(), table.size() * 4, hipMemcpyHostToDevice));
-    }
-    if (!as.shallow) {
-        std::vector<uint32_t> table(T * nin);
-        for (size_t q = 0; q < table.size(); ++q)
-            table[q] = (uint32_t)m->cut_feature[q] * xs << 8 | cut(q);
-        if (!r.recs) HIP_TRY(device_alloc(reinterpret_cast<void **>(&r.recs), table.size() * 4));
-        HIP_TRY(hipMemcpy(r.recs, table.data(), table.size() * 4, hipMemcpyHostToDevice));
-    }
+    // one allocation and one copy: the scalar records, then the per-node ones
+    const size_t words = as.shallow || !m->missing ? T * 16 : 0;
+    std::vector<uint32_t> table(words + (as.shallow ? 0 : T * nin), 0u);
+    for (size_t t = 0; words && t < T; ++t)
+        for (size_t k = 0; k < std::min<size_t>(nin, 7); ++k) {
+            const size_t q = t * nin + k;
+            table[t * 16 + k] = (uint32_t)m->cut_feature[q] * xs;
+            table[t * 16 + 8 + k] = (256u - cut(q)) * 0x01010101u;
+        }
+    for (size_t q = 0; !as.shallow && q < T * nin; ++q)
+        table[words + q] = (uint32_t)m->cut_feature[q] * xs << 8 | cut(q);
+    if (!r.nodes) HIP_TRY(device_alloc(reinterpret_cast<void **>(&r.nodes), table.size() * 4));
+    HIP_TRY(hipMemcpy(r.nodes, table.data(), table.size() * 4, hipMemcpyHostToDevice));
+    r.recs = as.shallow ? nullptr : r.nodes + words;
     r.stride = (int)xs;
     return FBDT_OK;
 }
@@ -1161,7 +1155,6 @@ int fbdt_model_import(const fbdt_model_view *v, fbdt_model **out) {
 
 static void free_records(fbdt_model::DeviceCopy::Records &r) {
     if (r.nodes) (void)hipFree(r.nodes);
-    if (r.recs) (void)hipFree(r.recs);
     r = {};
 }
 

@@ -34,7 +34,7 @@ constexpr int kQActive = 255;                   // active prefixes at most (one 
 constexpr int kQGroups = 256;                   // groups of 256 counters
 constexpr int kQGroupRow = 260;                 // group sums of a workgroup (padded)
 constexpr int kQBatch = 4;                      // 4-value vectors per thread and batch
-constexpr int kQCommon = 10;                    // crowded slots counted in registers
+constexpr int kQCommon = 6;                     // crowded slots counted by comparing
 // Values between two sweeps: a counter below 2^15 after a sweep cannot pass
 // 2^16 - 1 before the next one.
 constexpr int64_t kQSweep = 32768;
@@ -190,13 +190,14 @@ __device__ __forceinline__ void count_common(const uint32_t (&v)[kQBatch][4], co
 
 // Counts a batch in registers.  Values of few distinct codes put many lanes
 // of a wavefront on one counter, whose LDS atomic then takes about 8 clocks
-// per lane: where up to kQCommon slots hold half the lanes of the batch's
-// first value, count_common takes the batch.
+// per lane: where one of the first slots of the batch's first value holds 11
+// lanes or more, those of them with 4 or more go to count_common (comparing
+// costs about 6 clocks per slot, whatever its lanes).
 template <int LEVEL>
 __device__ __forceinline__ void count_batch(const uint32_t (&v)[kQBatch][4], const SlotSet &s1,
                                             const SlotSet &s2, uint32_t *cnt) {
     uint32_t common[kQCommon];
-    int nq = 0, covered = 0;
+    int nq = 0, most = 0;
     {
         uint32_t slot;
         const bool hit = value_slot<LEVEL>(v[0][0], s1, s2, slot);
@@ -204,17 +205,20 @@ __device__ __forceinline__ void count_batch(const uint32_t (&v)[kQBatch][4], con
 #pragma unroll
         for (int q = 0; q < kQCommon; ++q) {
             common[q] = ~0u;
-            if (left && (q == 0 || covered >= 3)) {
+            if (left && (q == 0 || most >= 3)) {
                 const uint32_t s = lane_value(slot, __ffsll((unsigned long long)left) - 1);
                 const uint64_t same = __ballot(hit && slot == s);
-                common[q] = s;
-                covered += __popcll(same);
+                const int many = __popcll(same);
                 left &= ~same;
-                nq = q + 1;
+                most = max(most, many);
+                if (many >= 4) {
+                    common[q] = s;
+                    nq = q + 1;
+                }
             }
         }
     }
-    if (covered < kQWave / 2) {
+    if (most < 11) {
 #pragma unroll
         for (int u = 0; u < kQBatch; ++u)
 #pragma unroll
@@ -224,8 +228,6 @@ __device__ __forceinline__ void count_batch(const uint32_t (&v)[kQBatch][4], con
             }
     } else if (nq <= 3) {
         count_common<LEVEL, 3>(v, s1, s2, cnt, common);
-    } else if (nq <= 6) {
-        count_common<LEVEL, 6>(v, s1, s2, cnt, common);
     } else {
         count_common<LEVEL, kQCommon>(v, s1, s2, cnt, common);
     }
