@@ -37,15 +37,21 @@ struct fbdt_model {
         // float apply: per-feature threshold table, or null
         uint32_t *ftab;
         int ftab_words;
-        // node records, or null, and the tile stride they were made for (0:
-        // none), of binned [0] and float [1] input, for launches that take the
-        // bulk [0] and the few-events kernel [1]: calls of both kinds may overlap
-        // and share none
+        // node records of binned [0] and float [1] input, per tile stride.  A
+        // call's stride follows from its number of events, and a launch on
+        // another stream or in a captured graph may read a record at any time:
+        // none is written twice, and the first call makes those of every
+        // stride that later ones can take (a capture allocates nothing).
         struct Records {
             int stride;
-            uint32_t *nodes;   // [T][16] (depth <= 3, or the first three levels)
-            uint32_t *recs;    // [T][2^D - 1] (deep kernels), in nodes' allocation
-        } rec[2][2];
+            uint32_t *nodes;   // [T][16] (depth <= 3, or the first three levels), or null
+            uint32_t *recs;    // [T][2^D - 1] (deep kernels), or null
+        };
+        struct RecordSet {
+            uint32_t *mem = nullptr;        // the allocation that holds all of at
+            std::vector<Records> at;
+        };
+        std::vector<RecordSet> rec[2];
     };
     std::mutex mu;
     std::vector<DeviceCopy> copies;
@@ -392,29 +398,54 @@ double list_algorithmic_bytes(int64_t n, double alpha, int d, int n_bins, int la
     return entries * (8.0 + d) + (double)hnodes * d * n_bins * 2 * 8;
 }
 
-// The node records of a launch shape, made on first use: `cut` gives a
-// node's bin, or the rank of its threshold.  Call with m->mu held.
+// The node records for the launch shape as, and for the other strides where
+// they are made: `cut` gives a node's bin, or the rank of its threshold.  Call
+// with m->mu held.
 template <typename Cut>
-int make_records(const fbdt_model *m, const ApplyShape &as, const Cut &cut,
-                        fbdt_model::DeviceCopy::Records &r) {
-    const uint32_t xs = (uint32_t)apply_node_stride(as);
-    if (r.stride == (int)xs) return FBDT_OK;
+int make_records(const fbdt_model *m, const ApplyShape &as, std::vector<int> strides,
+                 const Cut &cut, std::vector<fbdt_model::DeviceCopy::RecordSet> &sets,
+                 fbdt_model::DeviceCopy::Records *out) {
+    for (const auto &set : sets)
+        for (const auto &r : set.at)
+            if (r.stride == as.node_stride) {
+                *out = r;
+                return FBDT_OK;
+            }
+    // (a stride that is not among those of the first call: apply_threads was changed)
+    if (!sets.empty() || std::find(strides.begin(), strides.end(), as.node_stride) == strides.end())
+        strides.assign(1, as.node_stride);
     const size_t T = m->n_trees, nin = ((size_t)1 << m->depth) - 1;
-    // one allocation and one copy: the scalar records, then the per-node ones
+    // one allocation and one copy: per stride the scalar records, then the
+    // per-node ones, from a 64-byte boundary
     const size_t words = as.shallow || !m->missing ? T * 16 : 0;
-    std::vector<uint32_t> table(words + (as.shallow ? 0 : T * nin), 0u);
-    for (size_t t = 0; words && t < T; ++t)
-        for (size_t k = 0; k < std::min<size_t>(nin, 7); ++k) {
-            const size_t q = t * nin + k;
-            table[t * 16 + k] = (uint32_t)m->cut_feature[q] * xs;
-            table[t * 16 + 8 + k] = (256u - cut(q)) * 0x01010101u;
+    const size_t per = (words + (as.shallow ? 0 : T * nin) + 15) / 16 * 16;
+    std::vector<uint32_t> table(per * strides.size(), 0u);
+    for (size_t q = 0; q < T * nin; ++q) {
+        const uint32_t c = cut(q), f = m->cut_feature[q];
+        const size_t t = q / nin, k = q % nin;
+        for (size_t i = 0; i < strides.size(); ++i) {
+            uint32_t *const at = table.data() + i * per;
+            const uint32_t row = f * (uint32_t)strides[i];
+            if (words && k < 7) {
+                at[t * 16 + k] = row;
+                at[t * 16 + 8 + k] = (256u - c) * 0x01010101u;
+            }
+            if (!as.shallow) at[words + q] = row << 8 | c;
         }
-    for (size_t q = 0; !as.shallow && q < T * nin; ++q)
-        table[words + q] = (uint32_t)m->cut_feature[q] * xs << 8 | cut(q);
-    if (!r.nodes) HIP_TRY(device_alloc(reinterpret_cast<void **>(&r.nodes), table.size() * 4));
-    HIP_TRY(hipMemcpy(r.nodes, table.data(), table.size() * 4, hipMemcpyHostToDevice));
-    r.recs = as.shallow ? nullptr : r.nodes + words;
-    r.stride = (int)xs;
+    }
+    fbdt_model::DeviceCopy::RecordSet set;
+    HIP_TRY(device_alloc(reinterpret_cast<void **>(&set.mem), table.size() * 4));
+    const hipError_t e = hipMemcpy(set.mem, table.data(), table.size() * 4, hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+        (void)hipFree(set.mem);
+        HIP_TRY(e);
+    }
+    for (size_t i = 0; i < strides.size(); ++i) {
+        uint32_t *const at = set.mem + i * per;
+        set.at.push_back({strides[i], words ? at : nullptr, as.shallow ? nullptr : at + words});
+        if (strides[i] == as.node_stride) *out = set.at.back();
+    }
+    sets.push_back(std::move(set));
     return FBDT_OK;
 }
 
@@ -1153,9 +1184,9 @@ int fbdt_model_import(const fbdt_model_view *v, fbdt_model **out) {
     return FBDT_OK;
 }
 
-static void free_records(fbdt_model::DeviceCopy::Records &r) {
-    if (r.nodes) (void)hipFree(r.nodes);
-    r = {};
+static void free_records(std::vector<fbdt_model::DeviceCopy::RecordSet> &sets) {
+    for (auto &set : sets) (void)hipFree(set.mem);
+    sets.clear();
 }
 
 int fbdt_model_set_boundaries(fbdt_model *m, const float *boundaries) {
@@ -1172,7 +1203,7 @@ int fbdt_model_set_boundaries(fbdt_model *m, const float *boundaries) {
             if (c.ftab) (void)hipFree(c.ftab);
             c.ftab = nullptr;
             c.ftab_words = 0;
-            for (auto &r : c.rec[1]) free_records(r);
+            free_records(c.rec[1]);
         }
     if (cur >= 0) (void)hipSetDevice(cur);
     return FBDT_OK;
@@ -1188,8 +1219,7 @@ void fbdt_model_free(fbdt_model *m) {
             (void)hipFree(c.leaves);
             if (c.gains) (void)hipFree(c.gains);
             if (c.ftab) (void)hipFree(c.ftab);
-            for (auto &kind : c.rec)
-                for (auto &r : kind) free_records(r);
+            for (auto &sets : c.rec) free_records(sets);
         }
     }
     if (cur >= 0) (void)hipSetDevice(cur);
@@ -1264,10 +1294,13 @@ int fbdt_apply(const fbdt_model *mc, const uint8_t *xb, int64_t n, int32_t d, in
         std::lock_guard<std::mutex> lk(m->mu);
         fbdt_model::DeviceCopy *copy = nullptr;
         if ((rc = device_copy(m, dev, &copy))) return rc;
-        if ((rc = make_records(m, as, [&](size_t q) { return (uint32_t)m->cut_bin[q]; },
-                               copy->rec[0][as.split])))
+        const std::vector<int> strides =
+            copy->rec[0].empty() ? apply_node_strides(m->n_features, T, D, m->missing, di.cu_count,
+                                                      di.max_lds, (int)opt_apply_threads.load(), 0)
+                                 : std::vector<int>();
+        if ((rc = make_records(m, as, strides, [&](size_t q) { return (uint32_t)m->cut_bin[q]; },
+                               copy->rec[0], &r)))
             return rc;
-        r = copy->rec[0][as.split];
         leaves = copy->leaves;
     }
     Timed tm(FBDT_K_APPLY, s, (double)n * (m->n_features + 4));
@@ -1406,8 +1439,13 @@ int fbdt_apply_float(const fbdt_model *mc, const float *x, int64_t n, int32_t d,
             const auto &v = per[m->cut_feature[q]];
             return (uint32_t)(std::lower_bound(v.begin(), v.end(), threshold(q)) - v.begin()) + 1u;
         };
-        if ((rc = make_records(m, as, rank, copy->rec[1][as.split]))) return rc;
-        r = copy->rec[1][as.split];
+        const std::vector<int> strides =
+            copy->rec[1].empty()
+                ? apply_node_strides(m->n_features, T, D, m->missing, di.cu_count, di.max_lds,
+                                     (int)opt_apply_threads.load(),
+                                     (size_t)copy->ftab_words * sizeof(uint32_t))
+                : std::vector<int>();
+        if ((rc = make_records(m, as, strides, rank, copy->rec[1], &r))) return rc;
         ftab = copy->ftab;
         ftab_words = copy->ftab_words;
         leaves = copy->leaves;

@@ -6,6 +6,7 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <vector>
 
 namespace fbdt {
 
@@ -426,9 +427,9 @@ hipError_t launch_hist_list(const ListShape &ls, int lmode, const uint2 *list,
 // Forest traversal.  Forests of depth <= kApplyShallowDepth without missing
 // values take the shallow kernels, others the deep ones.  nodes (depth <= 3,
 // and the first three levels of deeper trees without missing values): [T][16],
-// for heap node k + 1 word k = feature * apply_node_stride (the LDS row offset
+// for heap node k + 1 word k = feature * node_stride (the LDS row offset
 // in the launch's code tile) and word 8 + k = (256 - bin) * 0x01010101.  recs
-// (deep kernels): [T][2^D - 1], feature * apply_node_stride << 8 | bin.
+// (deep kernels): [T][2^D - 1], feature * node_stride << 8 | bin.
 constexpr int kApplyShallowDepth = 3;
 // Rounds of one workgroup per CU up to which a traversal shares the trees of
 // 256 events among a workgroup's wavefronts: a round takes 14 us for 400 trees
@@ -450,7 +451,9 @@ struct ApplyShape {
 // table_bytes: the threshold table of a float input (0: binned).
 ApplyShape plan_apply(int64_t n, int d_used, int n_trees, int depth, bool missing,
                       int cu_count, size_t max_lds, int threads, size_t table_bytes = 0);
-inline int apply_node_stride(const ApplyShape &as) { return as.node_stride; }
+// Every node_stride that plan_apply gives for these arguments, over all n.
+std::vector<int> apply_node_strides(int d_used, int n_trees, int depth, bool missing, int cu_count,
+                                    size_t max_lds, int threads, size_t table_bytes);
 // Events: binned codes (xb, ldb), or float32 values (xf != null) with the
 // thresholds that the forest's cuts test: ftab = [d_used] words offset << 8 |
 // levels, then per feature, from its offset, 2^levels words: the ascending

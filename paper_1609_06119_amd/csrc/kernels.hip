@@ -18,6 +18,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdlib>
 #include <cstdint>
@@ -3826,17 +3827,38 @@ hipError_t launch_route(const uint8_t *xb, int64_t ldb, int64_t n, int d, uint8_
     return hipGetLastError();
 }
 
+// LDS bytes of an apply: of a tree's weights (and records), of the float
+// thresholds, and of the least part of the forest that a bulk launch stages.
+struct ApplyBytes {
+    int64_t per_tree, extra, least;
+};
+
+static ApplyBytes apply_bytes(int n_trees, int depth, bool missing, size_t table_bytes) {
+    // boost weights per tree: the leaves, or with missing values every node;
+    // the deep kernels also stage a record per node
+    const int nin = (1 << depth) - 1, nval = missing ? 2 * nin + 1 : nin + 1;
+    const bool shallow = depth <= kApplyShallowDepth && !missing;
+    ApplyBytes b;
+    b.per_tree = (int64_t)nval * 8 + (shallow ? 0 : (int64_t)nin * 4);
+    b.extra = ((int64_t)table_bytes + 15) & ~(int64_t)15;
+    b.least = std::max(std::min<int64_t>(n_trees * b.per_tree, 16384), b.per_tree);
+    return b;
+}
+
+// LDS left for trees by w workgroups per CU of t threads.
+static int64_t apply_room(const ApplyBytes &b, int d_used, size_t max_lds, int w, int t) {
+    return (int64_t)(max_lds / w) - (int64_t)kHistStaticLdsReserve - 64 - b.extra -
+           (int64_t)d_used * 4 * t;
+}
+
 ApplyShape plan_apply(int64_t n, int d_used, int n_trees, int depth, bool missing,
                       int cu_count, size_t max_lds, int threads, size_t table_bytes) {
     ApplyShape as{};
     as.d_used = d_used;
     as.missing = missing;
     as.shallow = depth <= kApplyShallowDepth && !missing;
-    // boost weights per tree: the leaves, or with missing values every node;
-    // the deep kernels also stage a record per node
-    const int nin = (1 << depth) - 1, nval = missing ? 2 * nin + 1 : nin + 1;
-    const int64_t per_tree = (int64_t)nval * 8 + (as.shallow ? 0 : (int64_t)nin * 4);
-    const int64_t extra = ((int64_t)table_bytes + 15) & ~(int64_t)15;   // float thresholds
+    const ApplyBytes bytes = apply_bytes(n_trees, depth, missing, table_bytes);
+    const int64_t per_tree = bytes.per_tree, extra = bytes.extra;
     const int64_t lds_cap = max_lds > kHistStaticLdsReserve ? max_lds - kHistStaticLdsReserve : 0;
     const auto trees = [&](int64_t room, int64_t bytes) {
         int64_t t = std::min<int64_t>(n_trees, room > 0 ? room / bytes : 0);
@@ -3863,14 +3885,11 @@ ApplyShape plan_apply(int64_t n, int d_used, int n_trees, int depth, bool missin
     // features: 1.02 ms with 24, 1.07 ms with 32).  A workgroup holds its
     // tile of codes and all trees' weights (and records), or at least 16 KiB
     // of them at a time.
-    const int64_t least = std::max(std::min<int64_t>(n_trees * per_tree, 16384), per_tree);
     double best = 0.0;
     int best_t = 0, best_w = 1;
     for (int w = 1; w <= 4; ++w)
         for (int t = 256; t <= 1024 && w * t <= 24 * kWave; t += 256) {
-            const int64_t room = (int64_t)(max_lds / w) - (int64_t)kHistStaticLdsReserve - 64 -
-                                 extra - (int64_t)d_used * 4 * t;
-            if (room < least) continue;
+            if (apply_room(bytes, d_used, max_lds, w, t) < bytes.least) continue;
             const int64_t round = 4 * (int64_t)t * w * cu_count;
             const double cost = (double)((n + round - 1) / round) *
                                 std::max(12.0, 6.5 + 0.75 * (w * t / kWave));
@@ -3897,6 +3916,26 @@ ApplyShape plan_apply(int64_t n, int d_used, int n_trees, int depth, bool missin
     if (blocks < 1) blocks = 1;
     as.blocks = (int)blocks;
     return as;
+}
+
+std::vector<int> apply_node_strides(int d_used, int n_trees, int depth, bool missing, int cu_count,
+                                    size_t max_lds, int threads, size_t table_bytes) {
+    std::vector<int> out;
+    const auto add = [&](int stride) {
+        if (std::find(out.begin(), out.end(), stride) == out.end()) out.push_back(stride);
+    };
+    // the few-events shape and the fixed or fallback one do not depend on n; the
+    // planned bulk ones are the workgroup sizes that fit a CU once
+    const ApplyShape few =
+        plan_apply(1, d_used, n_trees, depth, missing, cu_count, max_lds, threads, table_bytes);
+    const ApplyShape many = plan_apply((int64_t)1 << 40, d_used, n_trees, depth, missing, cu_count,
+                                       max_lds, threads, table_bytes);
+    add(few.node_stride);
+    add(many.node_stride);
+    const ApplyBytes bytes = apply_bytes(n_trees, depth, missing, table_bytes);
+    for (int t = 256; threads <= 0 && t <= 1024; t += 256)
+        if (apply_room(bytes, d_used, max_lds, 1, t) >= bytes.least) add(4 * t);
+    return out;
 }
 
 hipError_t launch_apply(const ApplyShape &as, const ApplyInput &in, const uint32_t *nodes,

@@ -98,6 +98,50 @@ def test_calls_of_few_and_many_events_interleave():
     assert torch.equal(p_few, p_big[:500])
 
 
+@pytest.mark.parametrize("d,D,T,missing,floats", [
+    (40, 3, 400, False, False), (8, 3, 100, False, True), (30, 6, 40, False, False),
+    (20, 4, 30, True, True),
+])
+def test_sizes_share_a_model(d, D, T, missing, floats):
+    """One warm-up call readies a model for captures of every size (other
+    sizes take other launch shapes and node records), and a captured call
+    replays after calls of other sizes."""
+    B = 200
+    f = random_forest(T, D, d, B, 11)
+    inner = np.random.default_rng(5).normal(0.0, 0.05, f["cut_bin"].shape) if missing else None
+    bounds = np.repeat(np.arange(1, B, dtype=np.float32)[None], d, axis=0)
+    m = fb.Model.from_arrays(f["cut_feature"], f["cut_bin"], f["leaf"], f["f0"], d, B,
+                             boundaries=bounds, inner=inner)
+    sizes = [500, 400_000, 700_000, 1_100_000, 1_700_000, 2_500_000]
+    xb = torch.randint(0, B, (d, sizes[-1]), dtype=torch.uint8, device="cuda")
+    x = xb.float() + 0.5
+    if missing:
+        x[:, ::7] = float("nan")
+
+    def call(n, prob):
+        if floats:
+            return fb.apply_float(m, x[:, :n], prob=prob)
+        return fb.apply(m, fb.Codes(xb, n), prob=prob)
+
+    call(500, torch.empty(500, device="cuda"))
+    torch.cuda.synchronize()
+    outs = [torch.zeros(n, device="cuda") for n in sizes]
+    graphs = []
+    for n, out in zip(sizes, outs):
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            call(n, out)
+        graphs.append(g)
+    whole = call(sizes[-1], torch.empty(sizes[-1], device="cuda"))
+    for _ in range(2):
+        for g in graphs:
+            g.replay()
+        torch.cuda.synchronize()
+        for n, out in zip(sizes, outs):
+            assert torch.equal(out, whole[:n]), n
+            out.zero_()
+
+
 @pytest.mark.parametrize("n,d,B,D,T,missing", [
     (1, 1, 2, 1, 1, False), (65, 40, 256, 3, 7, False), (100_001, 40, 256, 3, 230, False),
     (5_003, 255, 256, 5, 40, False), (20_011, 9, 200, 7, 33, True), (70_001, 3, 255, 2, 9, True),
