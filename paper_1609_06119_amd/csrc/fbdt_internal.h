@@ -439,6 +439,7 @@ constexpr int kSplitRounds = 6;
 struct ApplyShape {
     bool shallow;          // the shallow kernels
     bool split;            // the kernel for few events
+    bool table_far;        // the threshold table of a float input stays in memory
     bool missing;          // missing values: boost weights of every node per tree (heap
                            // order) and the missing code stops an event at its node
     int threads;

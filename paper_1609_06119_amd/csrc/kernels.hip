@@ -2543,10 +2543,13 @@ __device__ __forceinline__ void store_scores(const double (&F)[4], int64_t i0, i
     }
 }
 
-// With FLOATS the tile is staged from float32 values and the node records
+constexpr int kInCodes = 0, kInValues = 1, kInValuesFar = 2;
+// IN: what the tile is staged from.  kInValuesFar is for threshold tables that
+// would leave the LDS too little for a tile: its searches read the table
+// through the caches.  With float values the node records
 // carry, instead of the bin c, the rank c' of the node's threshold among its
 // feature's (code >= c' exactly when x >= threshold).
-template <int D, bool FLOATS>
+template <int D, int IN>
 __global__ __launch_bounds__(1024) void apply_shallow_kernel(
     const uint8_t *__restrict__ xb, int64_t ldb, const float *__restrict__ xf, int64_t ldx,
     const uint32_t *__restrict__ ftab, int ftab_words, int64_t n, int d_used,
@@ -2557,8 +2560,8 @@ __global__ __launch_bounds__(1024) void apply_shallow_kernel(
     double *s_leaf = smem;   // [tpc][NLEAF]
     uint8_t *s_x = reinterpret_cast<uint8_t *>(s_leaf + (size_t)tpc * NLEAF);   // [d_used][XS]
     const int XS = 4 * blockDim.x;   // the stride the node records were prepared for
-    uint32_t *s_tab = reinterpret_cast<uint32_t *>(s_x + (size_t)d_used * XS);   // FLOATS
-    if (FLOATS) {
+    uint32_t *s_tab = reinterpret_cast<uint32_t *>(s_x + (size_t)d_used * XS);   // kInValues
+    if (IN == kInValues) {
         for (int q = threadIdx.x; q < ftab_words; q += blockDim.x) s_tab[q] = ftab[q];
     }
     const int nchunks = (T + tpc - 1) / tpc;
@@ -2569,9 +2572,10 @@ __global__ __launch_bounds__(1024) void apply_shallow_kernel(
         const int64_t i0 = tile * XS + 4 * threadIdx.x;   // this thread's events
         // (a thread stages and reads its own words of the tile only; the
         // barrier publishes the threshold table)
-        if (FLOATS) {
+        if (IN != kInCodes) {
             if (!staged) __syncthreads();
-            stage_values<false>(s_x, XS, threadIdx.x, s_tab, xf, ldx, n, i0, 0, 1, d_used);
+            stage_values<false>(s_x, XS, threadIdx.x, IN == kInValuesFar ? ftab : s_tab,
+                                xf, ldx, n, i0, 0, 1, d_used);
         } else {
             stage_codes(s_x, XS, threadIdx.x, xb, ldb, n, i0, 0, 1, d_used);
         }
@@ -2633,7 +2637,7 @@ __global__ __launch_bounds__(1024) void apply_shallow_kernel(
 // 16 us; 260,000 events: 57 us, about 100 us in the bulk kernel).
 constexpr int kSplitEvents = 256;
 constexpr int kSplitThreads = 1024;
-template <int D, bool FLOATS>
+template <int D, int IN>
 __global__ __launch_bounds__(kSplitThreads) void apply_split_kernel(
     const uint8_t *__restrict__ xb, int64_t ldb, const float *__restrict__ xf, int64_t ldx,
     const uint32_t *__restrict__ ftab, int ftab_words, int64_t n, int d_used,
@@ -2646,13 +2650,16 @@ __global__ __launch_bounds__(kSplitThreads) void apply_split_kernel(
     double *s_leaf = smem;                                                       // [tpc][NLEAF]
     uint32_t *s_m = reinterpret_cast<uint32_t *>(s_leaf + (size_t)tpc * NLEAF);  // [tpc][kWave]
     uint8_t *s_x = reinterpret_cast<uint8_t *>(s_m + (size_t)tpc * kWave);       // [d_used][XS]
-    uint32_t *s_tab = reinterpret_cast<uint32_t *>(s_x + (size_t)d_used * XS);   // FLOATS
+    uint32_t *s_tab = reinterpret_cast<uint32_t *>(s_x + (size_t)d_used * XS);   // kInValues
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
     const int64_t base = (int64_t)blockIdx.x * kSplitEvents;
-    if (FLOATS) {
-        for (int q = threadIdx.x; q < ftab_words; q += kSplitThreads) s_tab[q] = ftab[q];
-        __syncthreads();
-        stage_values<false>(s_x, XS, lane, s_tab, xf, ldx, n, base + 4 * lane, wave, kWaves, d_used);
+    if (IN != kInCodes) {
+        if (IN == kInValues) {
+            for (int q = threadIdx.x; q < ftab_words; q += kSplitThreads) s_tab[q] = ftab[q];
+            __syncthreads();
+        }
+        stage_values<false>(s_x, XS, lane, IN == kInValuesFar ? ftab : s_tab,
+                            xf, ldx, n, base + 4 * lane, wave, kWaves, d_used);
     } else {
         stage_codes(s_x, XS, lane, xb, ldb, n, base + 4 * lane, wave, kWaves, d_used);
     }
@@ -2778,7 +2785,7 @@ __device__ __forceinline__ void stage_trees(double *s_leaf, uint32_t *s_rec, con
 // 100 trees of depth 6: 545 us, 1,110 us with one event per thread walking every
 // level; 2M events with a tenth of some features missing: 424 us, 580 us before.
 constexpr int kDeepBatch = 2;
-template <bool MISSING, bool FLOATS>
+template <bool MISSING, int IN>
 __global__ __launch_bounds__(1024) void apply_deep_kernel(
     const uint8_t *__restrict__ xb, int64_t ldb, const float *__restrict__ xf, int64_t ldx,
     const uint32_t *__restrict__ ftab, int ftab_words, int64_t n, int d_used,
@@ -2791,8 +2798,8 @@ __global__ __launch_bounds__(1024) void apply_deep_kernel(
     uint32_t *s_rec = reinterpret_cast<uint32_t *>(s_leaf + (size_t)tpc * nval);  // [tpc][nin]
     uint8_t *s_x = reinterpret_cast<uint8_t *>(s_rec + (size_t)tpc * nin);        // [d_used][XS]
     const int XS = 4 * blockDim.x;   // the stride the records were prepared for
-    uint32_t *s_tab = reinterpret_cast<uint32_t *>(s_x + (size_t)d_used * XS);    // FLOATS
-    if (FLOATS) {
+    uint32_t *s_tab = reinterpret_cast<uint32_t *>(s_x + (size_t)d_used * XS);    // kInValues
+    if (IN == kInValues) {
         for (int q = threadIdx.x; q < ftab_words; q += blockDim.x) s_tab[q] = ftab[q];
     }
     const int nchunks = (T + tpc - 1) / tpc;
@@ -2802,9 +2809,10 @@ __global__ __launch_bounds__(1024) void apply_deep_kernel(
     for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
         const int64_t i0 = tile * XS + 4 * threadIdx.x;   // this thread's events
         // (a thread stages and reads its own words of the tile only)
-        if (FLOATS) {
+        if (IN != kInCodes) {
             if (!staged) __syncthreads();
-            stage_values<MISSING>(s_x, XS, threadIdx.x, s_tab, xf, ldx, n, i0, 0, 1, d_used);
+            stage_values<MISSING>(s_x, XS, threadIdx.x, IN == kInValuesFar ? ftab : s_tab,
+                                  xf, ldx, n, i0, 0, 1, d_used);
         } else {
             stage_codes(s_x, XS, threadIdx.x, xb, ldb, n, i0, 0, 1, d_used);
         }
@@ -2842,7 +2850,7 @@ __global__ __launch_bounds__(1024) void apply_deep_kernel(
 }
 
 // The deep traversal for few events (see apply_split_kernel).
-template <bool MISSING, bool FLOATS>
+template <bool MISSING, int IN>
 __global__ __launch_bounds__(kSplitThreads) void apply_deep_split_kernel(
     const uint8_t *__restrict__ xb, int64_t ldb, const float *__restrict__ xf, int64_t ldx,
     const uint32_t *__restrict__ ftab, int ftab_words, int64_t n, int d_used,
@@ -2857,15 +2865,17 @@ __global__ __launch_bounds__(kSplitThreads) void apply_deep_split_kernel(
     uint32_t *s_rec = reinterpret_cast<uint32_t *>(s_leaf + (size_t)tpc * nval);  // [tpc][nin]
     uint32_t *s_m = s_rec + (size_t)tpc * nin;                                    // [tpc][kWave]
     uint8_t *s_x = reinterpret_cast<uint8_t *>(s_m + (size_t)tpc * kWave);        // [d_used][XS]
-    uint32_t *s_tab = reinterpret_cast<uint32_t *>(s_x + (size_t)d_used * XS);    // FLOATS
+    uint32_t *s_tab = reinterpret_cast<uint32_t *>(s_x + (size_t)d_used * XS);    // kInValues
     const int lane = threadIdx.x % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int64_t base = (int64_t)blockIdx.x * kSplitEvents;
-    if (FLOATS) {
-        for (int q = threadIdx.x; q < ftab_words; q += kSplitThreads) s_tab[q] = ftab[q];
-        __syncthreads();
-        stage_values<MISSING>(s_x, XS, lane, s_tab, xf, ldx, n, base + 4 * lane, wave, kWaves,
-                              d_used);
+    if (IN != kInCodes) {
+        if (IN == kInValues) {
+            for (int q = threadIdx.x; q < ftab_words; q += kSplitThreads) s_tab[q] = ftab[q];
+            __syncthreads();
+        }
+        stage_values<MISSING>(s_x, XS, lane, IN == kInValuesFar ? ftab : s_tab,
+                              xf, ldx, n, base + 4 * lane, wave, kWaves, d_used);
     } else {
         stage_codes(s_x, XS, lane, xb, ldb, n, base + 4 * lane, wave, kWaves, d_used);
     }
@@ -3181,26 +3191,36 @@ hipError_t prepare_kernels(size_t max_lds) {
                             allow_lds(leaf_kernel<true, 1>, max_lds),
                             allow_lds(leaf_kernel<true, 2>, max_lds),
                             allow_lds(leaf_kernel<true, 4>, max_lds),
-                            allow_lds(apply_shallow_kernel<1, false>, max_lds),
-                            allow_lds(apply_shallow_kernel<2, false>, max_lds),
-                            allow_lds(apply_shallow_kernel<3, false>, max_lds),
-                            allow_lds(apply_shallow_kernel<1, true>, max_lds),
-                            allow_lds(apply_shallow_kernel<2, true>, max_lds),
-                            allow_lds(apply_shallow_kernel<3, true>, max_lds),
-                            allow_lds(apply_split_kernel<1, false>, max_lds),
-                            allow_lds(apply_split_kernel<2, false>, max_lds),
-                            allow_lds(apply_split_kernel<3, false>, max_lds),
-                            allow_lds(apply_split_kernel<1, true>, max_lds),
-                            allow_lds(apply_split_kernel<2, true>, max_lds),
-                            allow_lds(apply_split_kernel<3, true>, max_lds),
-                            allow_lds(apply_deep_kernel<false, false>, max_lds),
-                            allow_lds(apply_deep_kernel<false, true>, max_lds),
-                            allow_lds(apply_deep_kernel<true, false>, max_lds),
-                            allow_lds(apply_deep_kernel<true, true>, max_lds),
-                            allow_lds(apply_deep_split_kernel<false, false>, max_lds),
-                            allow_lds(apply_deep_split_kernel<false, true>, max_lds),
-                            allow_lds(apply_deep_split_kernel<true, false>, max_lds),
-                            allow_lds(apply_deep_split_kernel<true, true>, max_lds),
+                            allow_lds(apply_shallow_kernel<1, kInCodes>, max_lds),
+                            allow_lds(apply_shallow_kernel<2, kInCodes>, max_lds),
+                            allow_lds(apply_shallow_kernel<3, kInCodes>, max_lds),
+                            allow_lds(apply_shallow_kernel<1, kInValues>, max_lds),
+                            allow_lds(apply_shallow_kernel<1, kInValuesFar>, max_lds),
+                            allow_lds(apply_shallow_kernel<2, kInValues>, max_lds),
+                            allow_lds(apply_shallow_kernel<2, kInValuesFar>, max_lds),
+                            allow_lds(apply_shallow_kernel<3, kInValues>, max_lds),
+                            allow_lds(apply_shallow_kernel<3, kInValuesFar>, max_lds),
+                            allow_lds(apply_split_kernel<1, kInCodes>, max_lds),
+                            allow_lds(apply_split_kernel<2, kInCodes>, max_lds),
+                            allow_lds(apply_split_kernel<3, kInCodes>, max_lds),
+                            allow_lds(apply_split_kernel<1, kInValues>, max_lds),
+                            allow_lds(apply_split_kernel<1, kInValuesFar>, max_lds),
+                            allow_lds(apply_split_kernel<2, kInValues>, max_lds),
+                            allow_lds(apply_split_kernel<2, kInValuesFar>, max_lds),
+                            allow_lds(apply_split_kernel<3, kInValues>, max_lds),
+                            allow_lds(apply_split_kernel<3, kInValuesFar>, max_lds),
+                            allow_lds(apply_deep_kernel<false, kInCodes>, max_lds),
+                            allow_lds(apply_deep_kernel<false, kInValues>, max_lds),
+                            allow_lds(apply_deep_kernel<false, kInValuesFar>, max_lds),
+                            allow_lds(apply_deep_kernel<true, kInCodes>, max_lds),
+                            allow_lds(apply_deep_kernel<true, kInValues>, max_lds),
+                            allow_lds(apply_deep_kernel<true, kInValuesFar>, max_lds),
+                            allow_lds(apply_deep_split_kernel<false, kInCodes>, max_lds),
+                            allow_lds(apply_deep_split_kernel<false, kInValues>, max_lds),
+                            allow_lds(apply_deep_split_kernel<false, kInValuesFar>, max_lds),
+                            allow_lds(apply_deep_split_kernel<true, kInCodes>, max_lds),
+                            allow_lds(apply_deep_split_kernel<true, kInValues>, max_lds),
+                            allow_lds(apply_deep_split_kernel<true, kInValuesFar>, max_lds),
                             allow_lds(importance_kernel<1, false>, max_lds),
                             allow_lds(importance_kernel<1, true>, max_lds),
                             allow_lds(importance_kernel<2, false>, max_lds),
@@ -3899,6 +3919,13 @@ ApplyShape plan_apply(int64_t n, int d_used, int n_trees, int depth, bool missin
                 best_w = w;
             }
         }
+    if (table_bytes > 0 && best_t == 0) {
+        // the threshold table takes the LDS that a tile for 256 threads needs
+        // (100 features with 200 thresholds each: 102 KB): it stays in memory
+        as = plan_apply(n, d_used, n_trees, depth, missing, cu_count, max_lds, threads, 0);
+        as.table_far = true;
+        return as;
+    }
     const bool planned = best_t > 0 && threads <= 0;
     int t = threads > 0 ? threads : best_t > 0 ? best_t : 256;
     while (t > 64 && (int64_t)d_used * 4 * t + per_tree + extra + 64 > lds_cap) t -= 64;
@@ -3932,7 +3959,8 @@ std::vector<int> apply_node_strides(int d_used, int n_trees, int depth, bool mis
                                        max_lds, threads, table_bytes);
     add(few.node_stride);
     add(many.node_stride);
-    const ApplyBytes bytes = apply_bytes(n_trees, depth, missing, table_bytes);
+    const ApplyBytes bytes =
+        apply_bytes(n_trees, depth, missing, many.table_far ? 0 : table_bytes);
     for (int t = 256; threads <= 0 && t <= 1024; t += 256)
         if (apply_room(bytes, d_used, max_lds, 1, t) >= bytes.least) add(4 * t);
     return out;
@@ -3944,7 +3972,7 @@ hipError_t launch_apply(const ApplyShape &as, const ApplyInput &in, const uint32
     const bool floats = in.xf != nullptr;
     const bool top = !as.missing && depth >= 3;   // scalar records of the first levels
     if ((as.shallow || top) && !nodes) return hipErrorInvalidValue;
-    if ((!as.shallow && !recs) || (floats && !in.ftab)) return hipErrorInvalidValue;
+    if ((!as.shallow && !recs) || (floats ? !in.ftab : !in.xb)) return hipErrorInvalidValue;
 #define FBDT_APPLY_ARGS                                                                         \
     in.xb, in.ldb, in.xf, in.ldx, in.ftab, in.ftab_words, in.n, as.d_used, nodes
 #define FBDT_APPLY_S(DV, FL)                                                                    \
@@ -3962,17 +3990,22 @@ hipError_t launch_apply(const ApplyShape &as, const ApplyInput &in, const uint32
     else                                                                                        \
         apply_deep_kernel<MI, FL><<<as.blocks, as.threads, as.lds_bytes, s>>>(                  \
             FBDT_APPLY_ARGS, recs, leaves, n_trees, depth, as.trees_per_chunk, f0, prob, score)
-    switch ((as.shallow ? depth : as.missing ? 5 : 4) + (floats ? 8 : 0)) {
-    case 1: FBDT_APPLY_S(1, false); break;
-    case 2: FBDT_APPLY_S(2, false); break;
-    case 3: FBDT_APPLY_S(3, false); break;
-    case 4: FBDT_APPLY_D(false, false); break;
-    case 5: FBDT_APPLY_D(true, false); break;
-    case 9: FBDT_APPLY_S(1, true); break;
-    case 10: FBDT_APPLY_S(2, true); break;
-    case 11: FBDT_APPLY_S(3, true); break;
-    case 12: FBDT_APPLY_D(false, true); break;
-    case 13: FBDT_APPLY_D(true, true); break;
+    switch ((as.shallow ? depth : as.missing ? 5 : 4) + (!floats ? 0 : as.table_far ? 16 : 8)) {
+    case 1: FBDT_APPLY_S(1, kInCodes); break;
+    case 2: FBDT_APPLY_S(2, kInCodes); break;
+    case 3: FBDT_APPLY_S(3, kInCodes); break;
+    case 4: FBDT_APPLY_D(false, kInCodes); break;
+    case 5: FBDT_APPLY_D(true, kInCodes); break;
+    case 9: FBDT_APPLY_S(1, kInValues); break;
+    case 10: FBDT_APPLY_S(2, kInValues); break;
+    case 11: FBDT_APPLY_S(3, kInValues); break;
+    case 12: FBDT_APPLY_D(false, kInValues); break;
+    case 13: FBDT_APPLY_D(true, kInValues); break;
+    case 17: FBDT_APPLY_S(1, kInValuesFar); break;
+    case 18: FBDT_APPLY_S(2, kInValuesFar); break;
+    case 19: FBDT_APPLY_S(3, kInValuesFar); break;
+    case 20: FBDT_APPLY_D(false, kInValuesFar); break;
+    case 21: FBDT_APPLY_D(true, kInValuesFar); break;
     default: return hipErrorInvalidValue;
     }
 #undef FBDT_APPLY_S

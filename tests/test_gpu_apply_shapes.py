@@ -143,6 +143,33 @@ def test_sizes_share_a_model(d, D, T, missing, floats):
 
 
 @pytest.mark.parametrize("n,d,B,D,T,missing", [
+    (1000, 255, 256, 3, 3000, False), (393_217, 160, 256, 3, 3000, False),
+    (259, 255, 256, 6, 300, False), (394_001, 100, 256, 6, 300, False),
+    (77, 255, 255, 7, 200, True), (393_219, 110, 255, 2, 4000, True),
+])
+def test_threshold_tables_beyond_the_lds(n, d, B, D, T, missing):
+    """Float values of forests whose thresholds do not fit the LDS beside a
+    tile score as their codes do."""
+    f = random_forest(T, D, d, B, n + T)
+    rng = np.random.default_rng([n, d, T, 2])
+    inner = rng.normal(0.0, 0.05, f["cut_bin"].shape) if missing else None
+    bounds = np.repeat(np.arange(1, B, dtype=np.float32)[None], d, axis=0)
+    m = fb.Model.from_arrays(f["cut_feature"], f["cut_bin"], f["leaf"], f["f0"], d, B,
+                             boundaries=bounds, inner=inner)
+    codes = fb.Codes.empty(d, n)
+    codes.data[:, :n] = torch.randint(0, B, (d, n), dtype=torch.uint8, device="cuda")
+    x = codes.data[:, :n].float() + 0.5
+    if missing:
+        codes.data[::3, :n:5] = 255
+        x[::3, ::5] = float("nan")
+    want = torch.empty(n, dtype=torch.float64, device="cuda")
+    score = torch.zeros_like(want)
+    fb.apply(m, codes, score=want)
+    fb.apply_float(m, x, score=score)
+    assert torch.equal(score, want)
+
+
+@pytest.mark.parametrize("n,d,B,D,T,missing", [
     (1, 1, 2, 1, 1, False), (65, 40, 256, 3, 7, False), (100_001, 40, 256, 3, 230, False),
     (5_003, 255, 256, 5, 40, False), (20_011, 9, 200, 7, 33, True), (70_001, 3, 255, 2, 9, True),
 ])
