@@ -3885,15 +3885,28 @@ ApplyShape plan_apply(int64_t n, int d_used, int n_trees, int depth, bool missin
         if (t < n_trees && t > kApplyBatch) t = t / kApplyBatch * kApplyBatch;
         return (int)t;
     };
-    const int64_t split_fixed = (int64_t)d_used * kSplitEvents + extra + 64;
+    const int64_t split_fixed = (int64_t)d_used * kSplitEvents + 64;
+    const auto split_trees = [&](int64_t table) {   // trees per chunk beside a table in LDS
+        return trees(lds_cap - split_fixed - table, per_tree + kWave * 4);
+    };
     if (threads <= 0 && n <= (int64_t)kSplitEvents * kSplitRounds * cu_count &&
-        trees(lds_cap - split_fixed, per_tree + kWave * 4) >= 1) {
-        // few events: the wavefronts of a workgroup share the trees
+        split_trees(0) >= 1) {
+        // few events: the wavefronts of a workgroup share the trees.  A float
+        // input's threshold table stays in memory where it would add more than 16
+        // chunks of trees, each with its barriers (500 events, table in LDS / in
+        // memory: 1,000 trees of depth 6, 80 features, 18 chunks for 8, 109 / 110
+        // us; 110 features, 48 chunks for 8, 137 / 117 us; 12,000 trees of depth
+        // 3, 126 features, 4,000 chunks for 30, 3,830 / 355 us)
+        const auto chunks = [&](int t) { return (n_trees + t - 1) / t; };
+        int tpc = split_trees(extra);
+        as.table_far = tpc < 1 || chunks(tpc) > chunks(split_trees(0)) + 16;
+        if (as.table_far) tpc = split_trees(0);
         as.split = true;
         as.threads = kSplitThreads;
         as.node_stride = kSplitEvents;
-        as.trees_per_chunk = trees(lds_cap - split_fixed, per_tree + kWave * 4);
-        as.lds_bytes = (size_t)(as.trees_per_chunk * (per_tree + kWave * 4) + split_fixed - 64);
+        as.trees_per_chunk = tpc;
+        as.lds_bytes = (size_t)(tpc * (per_tree + kWave * 4) + split_fixed - 64 +
+                                (as.table_far ? 0 : extra));
         as.blocks = (int)((n + kSplitEvents - 1) / kSplitEvents);
         return as;
     }

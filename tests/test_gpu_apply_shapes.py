@@ -146,6 +146,8 @@ def test_sizes_share_a_model(d, D, T, missing, floats):
     (1000, 255, 256, 3, 3000, False), (393_217, 160, 256, 3, 3000, False),
     (259, 255, 256, 6, 300, False), (394_001, 100, 256, 6, 300, False),
     (77, 255, 255, 7, 200, True), (393_219, 110, 255, 2, 4000, True),
+    # fits beside a few trees only: kept in memory for the chunks it would add
+    (500, 126, 256, 3, 12_000, False), (513, 110, 256, 6, 1000, False), (255, 118, 200, 7, 400, True),
 ])
 def test_threshold_tables_beyond_the_lds(n, d, B, D, T, missing):
     """Float values of forests whose thresholds do not fit the LDS beside a
@@ -187,3 +189,23 @@ def test_event_importance(n, d, B, D, T, missing):
                              inner=inner)
     got = fb.event_importance(m, fb.Codes.from_numpy(xb)).cpu().numpy()
     assert np.array_equal(got, O.event_importance(om, xb))
+
+
+@pytest.mark.parametrize("threads", [64, 192, 1024])
+@pytest.mark.parametrize("n,d,B,D,T", [(70_001, 160, 256, 3, 300), (5_003, 255, 256, 6, 40)])
+def test_requested_workgroup_sizes(n, d, B, D, T, threads):
+    """A workgroup size that is asked for scores as the planner's does, also
+    where the tile has to shrink to leave room for trees."""
+    f = random_forest(T, D, d, B, n + T)
+    bounds = np.repeat(np.arange(1, B, dtype=np.float32)[None], d, axis=0)
+    m = _model(f, d, B, bounds)
+    codes = fb.Codes.empty(d, n)
+    codes.data[:, :n] = torch.randint(0, B, (d, n), dtype=torch.uint8, device="cuda")
+    x = codes.data[:, :n].float() + 0.5
+    want = fb.apply(m, codes)
+    fb.set_option("apply_threads", threads)
+    try:
+        assert torch.equal(fb.apply(m, codes), want)
+        assert torch.equal(fb.apply_float(m, x), want)
+    finally:
+        fb.set_option("apply_threads", 0)

@@ -1,0 +1,108 @@
+"""Launch shapes of the library's planners, read from the built library's own
+planning functions (host code: no device is needed)."""
+import ctypes as C
+
+import pytest
+
+from paper_1609_06119_amd._lib import LIB_PATH
+
+CUS, LDS = 256, 160 * 1024          # compute units and LDS bytes of an MI355X
+RESERVE = 1024                      # LDS kept aside for static arrays
+SPLIT_EVENTS = 256                  # events of a few-events workgroup
+
+
+class ApplyShape(C.Structure):
+    _fields_ = [("shallow", C.c_bool), ("split", C.c_bool), ("table_far", C.c_bool),
+                ("missing", C.c_bool), ("threads", C.c_int), ("blocks", C.c_int),
+                ("trees_per_chunk", C.c_int), ("d_used", C.c_int), ("node_stride", C.c_int),
+                ("lds_bytes", C.c_size_t)]
+
+
+class IntVector(C.Structure):       # std::vector<int>: begin, end, end of storage
+    _fields_ = [("begin", C.POINTER(C.c_int)), ("end", C.POINTER(C.c_int)), ("cap", C.c_void_p)]
+
+
+@pytest.fixture(scope="module")
+def planner():
+    lib = C.CDLL(LIB_PATH)
+    plan = getattr(lib, "_ZN4fbdt10plan_applyEliiibimim")
+    plan.restype = ApplyShape
+    plan.argtypes = [C.c_int64, C.c_int, C.c_int, C.c_int, C.c_bool, C.c_int, C.c_size_t, C.c_int,
+                     C.c_size_t]
+    strides = getattr(lib, "_ZN4fbdt18apply_node_stridesEiiibimim")
+    strides.restype = IntVector
+    strides.argtypes = plan.argtypes[1:]
+
+    class Planner:
+        def apply(self, n, d, T, D, missing=False, threads=0, table=0):
+            return plan(n, d, T, D, missing, CUS, LDS, threads, table)
+
+        def strides(self, d, T, D, missing=False, threads=0, table=0):
+            v = strides(d, T, D, missing, CUS, LDS, threads, table)
+            count = (C.cast(v.end, C.c_void_p).value - C.cast(v.begin, C.c_void_p).value) // 4
+            return [v.begin[k] for k in range(count)]
+
+    return Planner()
+
+
+def tree_bytes(s, D):
+    """LDS bytes of a tree: its boost weights, and the deep kernels' records."""
+    nin = (1 << D) - 1
+    return (2 * nin + 1 if s.missing else nin + 1) * 8 + (0 if s.shallow else nin * 4)
+
+
+FORESTS = [(1, 1, False), (10, 1, False), (400, 3, False), (3000, 3, False), (100, 4, False),
+           (100, 6, False), (1000, 7, False), (300, 2, True), (200, 7, True)]
+WIDTHS = [1, 2, 5, 13, 40, 60, 79, 80, 100, 125, 142, 143, 150, 155, 156, 157, 158, 159, 160, 180,
+          210, 211, 212, 254, 255]
+EVENTS = [1, 255, 256, 257, 65_536, 393_216, 393_217, 600_000, 1_300_001, 50_000_000, 1 << 33]
+
+
+def table_bytes(d, levels):
+    """A float input's table with 2^levels words of thresholds per feature."""
+    return 4 * d * (1 + (1 << levels))
+
+
+@pytest.mark.parametrize("T,D,missing", FORESTS)
+def test_apply_shapes_hold(planner, T, D, missing):
+    """Every shape fits the LDS and the launch limits, covers its events, and
+    has the node records that the model's first call makes."""
+    for d in WIDTHS:
+        for table in (0, table_bytes(d, 1), table_bytes(d, 5), table_bytes(d, 7), table_bytes(d, 8)):
+            known = set(planner.strides(d, T, D, missing, 0, table))
+            for n in EVENTS:
+                s = planner.apply(n, d, T, D, missing, 0, table)
+                what = (d, table, n)
+                extra = 0 if s.table_far else (table + 15) // 16 * 16
+                per = tree_bytes(s, D) + (SPLIT_EVENTS if s.split else 0)
+                events = SPLIT_EVENTS if s.split else 4 * s.threads
+                assert s.shallow == (D <= 3 and not missing), what
+                assert s.threads % 64 == 0 and 64 <= s.threads <= 1024, what
+                assert 1 <= s.trees_per_chunk <= T, what
+                assert s.lds_bytes >= s.trees_per_chunk * per + d * events + extra, what
+                assert s.lds_bytes + RESERVE <= LDS, what
+                assert s.node_stride == events and s.node_stride in known, what
+                assert s.blocks >= 1 and s.blocks * s.threads < 1 << 32, what
+                if s.split:
+                    assert s.blocks * SPLIT_EVENTS >= n, what
+                assert table or not s.table_far, what
+
+
+@pytest.mark.parametrize("T,D,missing", FORESTS + [(12_000, 3, False), (12_000, 2, False)])
+def test_a_threshold_table_leaves_room_for_trees(planner, T, D, missing):
+    """A few-events launch keeps the threshold table of float values in LDS
+    only where that adds at most 16 chunks of trees to the launch."""
+    near = 0
+    for d in range(1, 256):
+        plain = planner.apply(500, d, T, D, missing, 0, 0)
+        assert plain.split
+        for levels in range(1, 9):
+            s = planner.apply(500, d, T, D, missing, 0, table_bytes(d, levels))
+            what = (d, levels, s.trees_per_chunk)
+            assert s.split, what
+            if s.table_far:
+                assert s.trees_per_chunk == plain.trees_per_chunk, what
+            else:
+                near += 1
+                assert -(-T // s.trees_per_chunk) <= -(-T // plain.trees_per_chunk) + 16, what
+    assert near > 0
