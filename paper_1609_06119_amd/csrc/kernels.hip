@@ -3865,6 +3865,12 @@ static ApplyBytes apply_bytes(int n_trees, int depth, bool missing, size_t table
     return b;
 }
 
+// Wavefronts per CU that a bulk traversal has to hold, and the events up to
+// which the traversal of few events stands in for it (a grid holds fewer than
+// 2^32 threads, 4 per event there).
+constexpr int kBulkWaves = 8;
+constexpr int64_t kSplitMostEvents = (int64_t)1 << 29;
+
 // LDS left for trees by w workgroups per CU of t threads.
 static int64_t apply_room(const ApplyBytes &b, int d_used, size_t max_lds, int w, int t) {
     return (int64_t)(max_lds / w) - (int64_t)kHistStaticLdsReserve - 64 - b.extra -
@@ -3885,31 +3891,6 @@ ApplyShape plan_apply(int64_t n, int d_used, int n_trees, int depth, bool missin
         if (t < n_trees && t > kApplyBatch) t = t / kApplyBatch * kApplyBatch;
         return (int)t;
     };
-    const int64_t split_fixed = (int64_t)d_used * kSplitEvents + 64;
-    const auto split_trees = [&](int64_t table) {   // trees per chunk beside a table in LDS
-        return trees(lds_cap - split_fixed - table, per_tree + kWave * 4);
-    };
-    if (threads <= 0 && n <= (int64_t)kSplitEvents * kSplitRounds * cu_count &&
-        split_trees(0) >= 1) {
-        // few events: the wavefronts of a workgroup share the trees.  A float
-        // input's threshold table stays in memory where it would add more than 16
-        // chunks of trees, each with its barriers (500 events, table in LDS / in
-        // memory: 1,000 trees of depth 6, 80 features, 18 chunks for 8, 109 / 110
-        // us; 110 features, 48 chunks for 8, 137 / 117 us; 12,000 trees of depth
-        // 3, 126 features, 4,000 chunks for 30, 3,830 / 355 us)
-        const auto chunks = [&](int t) { return (n_trees + t - 1) / t; };
-        int tpc = split_trees(extra);
-        as.table_far = tpc < 1 || chunks(tpc) > chunks(split_trees(0)) + 16;
-        if (as.table_far) tpc = split_trees(0);
-        as.split = true;
-        as.threads = kSplitThreads;
-        as.node_stride = kSplitEvents;
-        as.trees_per_chunk = tpc;
-        as.lds_bytes = (size_t)(tpc * (per_tree + kWave * 4) + split_fixed - 64 +
-                                (as.table_far ? 0 : extra));
-        as.blocks = (int)((n + kSplitEvents - 1) / kSplitEvents);
-        return as;
-    }
     // the workgroup size and workgroups per CU of least rounds x time.  A
     // round of W wavefronts per CU takes about 6.5 + 0.75 W (W = 24 most, at
     // least 12 in these units of 7 us for 400 trees of depth 3): the traversal
@@ -3932,6 +3913,37 @@ ApplyShape plan_apply(int64_t n, int d_used, int n_trees, int depth, bool missin
                 best_w = w;
             }
         }
+    const int64_t split_fixed = (int64_t)d_used * kSplitEvents + 64;
+    const auto split_trees = [&](int64_t table) {   // trees per chunk beside a table in LDS
+        return trees(lds_cap - split_fixed - table, per_tree + kWave * 4);
+    };
+    // few events, or a forest whose code tile leaves the bulk kernel few wavefronts
+    // per CU: a workgroup of 16 wavefronts takes 256 events and its wavefronts
+    // share the trees.  1.5M events, bulk / shared: 60 features (8 wavefronts) 279
+    // / 283 us for 400 trees of depth 3, 240 / 251 us for 100 of depth 6; 80
+    // features (4) 510 / 293 and 407 / 261 us; 255 features (2) 1,729 / 395 and
+    // 1,583 / 375 us; float values of 255 features, 10 trees of depth 1, 705 / 255 us.
+    const bool few = n <= (int64_t)kSplitEvents * kSplitRounds * cu_count;
+    const bool thin = best_t * best_w < kBulkWaves * kWave && n <= kSplitMostEvents;
+    if (threads <= 0 && (few || thin) && split_trees(0) >= 1) {
+        // a float input's threshold table stays in memory where it would add more
+        // than 16 chunks of trees, each with its barriers (500 events, table in LDS /
+        // in memory: 1,000 trees of depth 6, 80 features, 18 chunks for 8, 109 / 110
+        // us; 110 features, 48 chunks for 8, 137 / 117 us; 12,000 trees of depth
+        // 3, 126 features, 4,000 chunks for 30, 3,830 / 355 us)
+        const auto chunks = [&](int t) { return (n_trees + t - 1) / t; };
+        int tpc = split_trees(extra);
+        as.table_far = tpc < 1 || chunks(tpc) > chunks(split_trees(0)) + 16;
+        if (as.table_far) tpc = split_trees(0);
+        as.split = true;
+        as.threads = kSplitThreads;
+        as.node_stride = kSplitEvents;
+        as.trees_per_chunk = tpc;
+        as.lds_bytes = (size_t)(tpc * (per_tree + kWave * 4) + split_fixed - 64 +
+                                (as.table_far ? 0 : extra));
+        as.blocks = (int)((n + kSplitEvents - 1) / kSplitEvents);
+        return as;
+    }
     if (table_bytes > 0 && best_t == 0) {
         // the threshold table takes the LDS that a tile for 256 threads needs
         // (100 features with 200 thresholds each: 102 KB): it stays in memory

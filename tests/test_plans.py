@@ -88,6 +88,20 @@ def test_apply_shapes_hold(planner, T, D, missing):
                 assert table or not s.table_far, what
 
 
+@pytest.mark.parametrize("T,D,missing", FORESTS)
+def test_a_bulk_launch_fills_the_compute_units(planner, T, D, missing):
+    """A bulk launch holds at least 8 wavefronts per compute unit: where the
+    code tile of a wide forest or the threshold table of float values leaves
+    room for fewer, the wavefronts of a few-events launch share the trees."""
+    for d in range(1, 256):
+        for levels in (0, 2, 5, 8):
+            table = table_bytes(d, levels) if levels else 0
+            for n in (393_217, 2_000_000, 50_000_000):
+                s = planner.apply(n, d, T, D, missing, 0, table)
+                per_cu = LDS // (s.lds_bytes + RESERVE)
+                assert s.split or per_cu * s.threads >= 8 * 64, (d, levels, n, s.threads)
+
+
 @pytest.mark.parametrize("T,D,missing", FORESTS + [(12_000, 3, False), (12_000, 2, False)])
 def test_a_threshold_table_leaves_room_for_trees(planner, T, D, missing):
     """A few-events launch keeps the threshold table of float values in LDS
