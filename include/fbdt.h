@@ -320,12 +320,15 @@ int fbdt_timing_read(int32_t kind, int64_t *launches, double *total_ms, double *
  * Names: "hist_features_per_group" (1, 2, 4, 5 or 8), "hist_event_chunks",
  * "hist_threads" (a multiple of 64, at most 1024), "hist_copies" (1, 2 or 4
  * LDS copies of a workgroup's histograms), "apply_threads".
- * "fit_graphs" (default 1): fbdt_fit records the kernel launches of its
- * boosting loop as a HIP graph on first use of an argument set (device,
- * buffer addresses, sizes, parameters, launch shapes) and replays it on later
- * calls with the same set; up to 4 graphs per device are kept, and growing the
- * device workspace drops them.  0 launches every kernel one by one.  Graphs
- * are not used while any fit kernel kind is being timed.
+ * "fit_graphs" (default 1): fbdt_fit can record the kernel launches of its
+ * boosting loop as a HIP graph of an argument set (device, buffer addresses,
+ * sizes, parameters, launch shapes) and replay it on later calls with the
+ * same set; up to 4 graphs per device are kept, and growing the device
+ * workspace drops them.  1 records a set of up to 2^24 codes (n * d) once 32
+ * calls with it have launched their kernels one by one (recording costs as
+ * much as these lost, and larger fits gain nothing by it); 2 or more records
+ * every set on first use; 0 launches every kernel one by one.  Graphs are not
+ * used while any fit kernel kind is being timed.
  * "fail_alloc" (default 0, for tests of the error path): the next `value`
  * device allocations the library would make (its scratch, a model's device
  * copy) fail instead, and the calls that needed them return FBDT_E_DEVICE;

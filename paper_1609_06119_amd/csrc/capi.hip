@@ -249,24 +249,59 @@ struct GraphKey {
     }
 };
 
+// Direct launches of the fits with some arguments since their loop was last
+// dropped from (or never was in) the graphs.
+struct DirectFits {
+    GraphKey key;
+    int fits;
+};
+
 struct Arena {
     std::mutex mu;
     void *ptr = nullptr;
     size_t size = 0;
     std::vector<std::pair<GraphKey, hipGraphExec_t>> graphs;  // oldest first
-    std::vector<GraphKey> once;   // arguments of fits launched directly, oldest first
+    std::vector<DirectFits> direct;   // latest last
     void *host = nullptr;         // pinned: results on their way to the caller
     size_t host_size = 0;
     hipStream_t capture = nullptr;  // records launches only; never runs work
 };
 Arena g_arena[64];
 constexpr size_t kMaxGraphs = 4;
-constexpr size_t kMaxOnce = 8;
+constexpr size_t kMaxDirect = 8;
+// When a fit captures by itself.  Capturing and instantiating the loop costs
+// 2.7 to 3.4 us per launch once; a replay saves 0.2 us per launch where the
+// kernels are short and nothing where they are long.  Direct / capturing /
+// replaying call, and the fits that repay the capture: 10k x 8 events, 10 trees
+// of depth 3, 438 / 662 / 425 us, 18; 100 trees 3.91 / 6.44 / 3.74 ms, 16; 100k x
+// 20, 100 trees 4.69 / 7.83 / 4.59 ms, 31; 500k x 20 5.88 / 8.55 / 5.82 ms, 45; 2M x
+// 40 12.64 / 15.15 / 12.62 ms, over 100; 10M x 40, depth 6: none.  So only fits
+// of up to kGraphCodes codes capture (1% saved at 10M codes, 0.15% at 80M), after
+// kCaptureAfter direct launches: what the direct launches lost by then
+// is about what the capture costs, and a program that fits a few times never
+// pays it.
+constexpr int kCaptureAfter = 32;
+constexpr int64_t kGraphCodes = (int64_t)1 << 24;
 
 void drop_graphs(Arena &a) {
     for (auto &g : a.graphs) (void)hipGraphExecDestroy(g.second);
     a.graphs.clear();
-    a.once.clear();
+    a.direct.clear();
+}
+
+// Counts a fit of these arguments (those of the last kMaxDirect sets are kept);
+// returns the direct launches before it.
+int count_direct(Arena &a, const GraphKey &key) {
+    int before = 0;
+    for (auto it = a.direct.begin(); it != a.direct.end(); ++it)
+        if (it->key == key) {
+            before = it->fits;
+            a.direct.erase(it);
+            break;
+        }
+    if (a.direct.size() >= kMaxDirect) a.direct.erase(a.direct.begin());
+    a.direct.push_back({key, before + 1});
+    return before;
 }
 
 // Pinned host memory of at least `bytes` (a copy from the device into it
@@ -499,7 +534,7 @@ int fbdt_set_option(const char *name, int64_t value) {
         }
         opt_fail_alloc = value;
     } else if (!strcmp(name, "fit_graphs")) {
-        opt_fit_graphs = value != 0;
+        opt_fit_graphs = value;
     } else if (!strcmp(name, "apply_threads")) {
         if (value != 0 && (value % 64 != 0 || value > 1024))
             return fail(FBDT_E_INVAL, "apply_threads must be a multiple of 64, <= 1024");
@@ -1006,7 +1041,8 @@ int fbdt_fit(const uint8_t *xb, int64_t n, int32_t d, int64_t ldb, int32_t n_bin
     };
     const int timed_kinds = (1 << FBDT_K_TREE_PREP) | (1 << FBDT_K_HISTOGRAM) |
                             (1 << FBDT_K_BEST_CUTS) | (1 << FBDT_K_LEAF) | (1 << FBDT_K_ROUTE);
-    if (opt_fit_graphs.load() && !timeline && !(g_timing.load() & timed_kinds)) {
+    const int64_t graphs = opt_fit_graphs.load();
+    if (graphs && !timeline && !(g_timing.load() & timed_kinds)) {
         const GraphKey key{xb, y, w, n, ldb, d, n_bins, D, T, scale, lblocks, eta, alpha, seed,
                            opt_hist_fpg.load(), opt_hist_chunks.load(), opt_hist_threads.load(),
                            opt_hist_copies.load(), signed_w, missing, lists,
@@ -1014,16 +1050,11 @@ int fbdt_fit(const uint8_t *xb, int64_t n, int32_t d, int64_t ldb, int32_t n_bin
         hipGraphExec_t exec = nullptr;
         for (auto &g : a.graphs)
             if (g.first == key) exec = g.second;
-        // Capturing and instantiating the loop costs more than it saves until
-        // it has been replayed a few times (500k events, 100 trees: 2.4 ms once,
-        // 0.08 to 0.15 ms less per fit; 10k events, 10 trees: 0.3 and 0.05 ms): the
-        // first fit with some arguments launches kernel by kernel, and only
-        // one that repeats them captures.
-        bool repeated = exec != nullptr;
-        for (auto &k : a.once) repeated = repeated || k == key;
-        if (!repeated) {
-            if (a.once.size() >= kMaxOnce) a.once.erase(a.once.begin());
-            a.once.push_back(key);
+        // (option value 2 or more: recorded on first use)
+        const bool capture =
+            !exec && (graphs > 1 || ((int64_t)d * n <= kGraphCodes &&
+                                     count_direct(a, key) >= kCaptureAfter));
+        if (!exec && !capture) {
             if ((rc = enqueue_trees(s))) return rc;
         } else if (!exec) {
             // captured on a stream of the library's own, since the caller's may
@@ -1050,6 +1081,10 @@ int fbdt_fit(const uint8_t *xb, int64_t n, int32_t d, int64_t ldb, int32_t n_bin
                 a.graphs.erase(a.graphs.begin());
             }
             a.graphs.push_back({key, exec});
+            // (counted afresh when this one is dropped)
+            a.direct.erase(std::remove_if(a.direct.begin(), a.direct.end(),
+                                          [&](const DirectFits &q) { return q.key == key; }),
+                           a.direct.end());
         }
         if (exec) HIP_TRY(hipGraphLaunch(exec, s));
     } else if ((rc = enqueue_trees(s))) {

@@ -184,7 +184,7 @@ def test_list_fit_graph_replays_match_eager_fit():
     fb.set_option("hist_lists", 2)
     fb.set_option("fit_graphs", 0)
     ref = fb.fit(codes, y, 256, 6, 3, 0.1, 0.5, 4, w=v).export()
-    fb.set_option("fit_graphs", 1)
+    fb.set_option("fit_graphs", 2)              # captured on first use
     for rep in range(3):
         got = fb.fit(codes, y, 256, 6, 3, 0.1, 0.5, 4, w=v).export()
         torch.cuda.synchronize()
