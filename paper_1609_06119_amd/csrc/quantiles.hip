@@ -41,10 +41,12 @@ constexpr int64_t kQSweep = 32768;
 // Values a workgroup may count without a sweep (16-bit counters).
 constexpr int64_t kQNoSweep = 65280;
 // Values up to which one workgroup per feature does everything: above, the
-// six launches of the shared counts cost less than one CU's counting
-// (60,000 x 20 values: 82 us in one workgroup per feature, 68 us shared;
-// 20,000 x 8: 42 us in one).
-constexpr int64_t kQSmall = 20480;
+// six launches of the shared counts get closer.  Time in one workgroup per
+// feature over the time shared, over 1 to 255 features of normal values and of
+// five levels: 0.53 to 0.81 at 20,000 values, 0.56 to 1.00 at 32,000, 0.58 to
+// 1.00 at 40,000, 0.61 to 1.10 at 50,000, 0.62 to 1.17 at 60,000 (the larger
+// ones for few features of few levels).
+constexpr int64_t kQSmall = 40960;
 static_assert(kQSmall <= kQNoSweep, "the one-workgroup path does not sweep");
 static_assert(kQSweep == (int64_t)2 * kQBatch * 4 * kQThreads, "two batches between sweeps");
 

@@ -34,7 +34,10 @@ def _values(kind, n, d, rng):
 
 @pytest.mark.parametrize("n,d,n_bins,kind", [
     (1, 1, 2, "plain"), (3, 2, 256, "mixed"), (1023, 5, 256, "mixed"), (4097, 3, 17, "nan"),
-    (20_480, 3, 256, "mixed"), (20_481, 3, 256, "mixed"), (65_280, 4, 256, "mixed"), (65_281, 4, 256, "mixed"), (65_283, 3, 255, "nan"),
+    (20_480, 3, 256, "mixed"), (20_481, 3, 256, "mixed"),
+    # the last size that one workgroup per feature counts alone, and the next
+    (40_960, 8, 256, "mixed"), (40_960, 5, 200, "nan"), (40_961, 8, 256, "mixed"),
+    (65_280, 4, 256, "mixed"), (65_281, 4, 256, "mixed"), (65_283, 3, 255, "nan"),
     (300_001, 7, 100, "nan"), (777_777, 9, 256, "mixed"),
     (4_000_001, 8, 256, "mixed"),     # 125,000 values per workgroup: swept counters
     (2_500_000, 40, 200, "nan"),

@@ -120,3 +120,26 @@ def test_a_threshold_table_leaves_room_for_trees(planner, T, D, missing):
                 near += 1
                 assert -(-T // s.trees_per_chunk) <= -(-T // plain.trees_per_chunk) + 16, what
     assert near > 0
+
+
+class QuantileShape(C.Structure):
+    _fields_ = [("small", C.c_bool), ("chunks", C.c_int), ("per", C.c_int64)]
+
+
+@pytest.fixture(scope="module")
+def quantile_plan():
+    plan = C.CDLL(LIB_PATH)._ZN4fbdt14plan_quantilesElii
+    plan.restype = QuantileShape
+    plan.argtypes = [C.c_int64, C.c_int, C.c_int]
+    return lambda n, d: plan(n, d, CUS)
+
+
+def test_quantile_shapes_cover_their_values(quantile_plan):
+    for d in (1, 2, 7, 8, 40, 100, 255):
+        for n in (1, 20_480, 40_960, 40_961, 65_281, 300_001, 4_000_001, 50_000_000, 1 << 33):
+            q = quantile_plan(n, d)
+            assert q.small == (n <= 40_960), (n, d)
+            if not q.small:
+                assert 1 <= q.chunks <= 256 and q.per % 4 == 0, (n, d)
+                assert (q.chunks - 1) * q.per < n <= q.chunks * q.per, (n, d)
+                assert q.per <= 1 << 31, (n, d)
