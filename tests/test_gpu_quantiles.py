@@ -25,11 +25,17 @@ def _values(kind, n, d, rng):
                 x[j] = 1000.0 + x[j] * 1e-3                   # one 16-bit prefix
             some = rng.integers(0, n, max(1, n // 50))
             x[j, some] = special[rng.integers(0, 8, some.size)]
+    elif kind == "half":
+        x[:, rng.random(n) < 0.5] = 0.25
     elif kind == "nan":
         for j in range(d):
             x[j, rng.random(n) < (0.3 * j) % 1.1] = np.nan
         x[d - 1] = np.nan
     return x
+
+
+# more than 65,280 values per workgroup (test_plans.py checks that they are)
+SWEPT = [(1_000_003, 40, 256, "mixed"), (2_500_000, 40, 200, "nan"), (16_711_681, 1, 256, "half")]
 
 
 @pytest.mark.parametrize("n,d,n_bins,kind", [
@@ -39,8 +45,10 @@ def _values(kind, n, d, rng):
     (40_960, 8, 256, "mixed"), (40_960, 5, 200, "nan"), (40_961, 8, 256, "mixed"),
     (65_280, 4, 256, "mixed"), (65_281, 4, 256, "mixed"), (65_283, 3, 255, "nan"),
     (300_001, 7, 100, "nan"), (777_777, 9, 256, "mixed"),
-    (4_000_001, 8, 256, "mixed"),     # 125,000 values per workgroup: swept counters
-    (2_500_000, 40, 200, "nan"),
+    (4_000_001, 8, 256, "mixed"),     # 62,504 values per workgroup: close to the 16-bit limit
+    # beyond it: swept counters, of crowded slots at every digit, of NaN, and
+    # with a last workgroup whose own values would need no sweep
+    *SWEPT,
 ])
 def test_bin_matches_oracle(n, d, n_bins, kind):
     rng = np.random.default_rng([n, d, n_bins])

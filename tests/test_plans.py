@@ -143,3 +143,15 @@ def test_quantile_shapes_cover_their_values(quantile_plan):
                 assert 1 <= q.chunks <= 256 and q.per % 4 == 0, (n, d)
                 assert (q.chunks - 1) * q.per < n <= q.chunks * q.per, (n, d)
                 assert q.per <= 1 << 31, (n, d)
+
+
+def test_the_swept_cases_sweep(quantile_plan):
+    """The binning tests' cases of long chunks take the 32-bit counters, and
+    one of them has a last chunk that needs none for itself."""
+    from test_gpu_quantiles import SWEPT
+    last = []
+    for n, d, _, _ in SWEPT:
+        q = quantile_plan(n, d)
+        assert q.per > 65_280, (n, d)
+        last.append(n - (q.chunks - 1) * q.per)
+    assert min(last) <= 65_280
