@@ -334,7 +334,8 @@ int fbdt_timing_read(int32_t kind, int64_t *launches, double *total_ms, double *
  * copy) fail instead, and the calls that needed them return FBDT_E_DEVICE;
  * a positive value first releases the scratch the library holds (waiting
  * for the devices to finish with it), so the next call that needs scratch
- * allocates.
+ * allocates.  "fail_host_alloc": the same for the pinned host memory through
+ * which fits return their results.
  * "hist_timeline" (default 0): 1 makes fbdt_fit record the phase timeline
  * of every histogram launch (see fbdt_hist_timeline); fits then launch
  * kernel by kernel and stream every layer (no event lists).

@@ -124,20 +124,37 @@ int device_info(int dev, DeviceInfo *out) {
 }
 
 // ---- options --------------------------------------------------------------
-// Forced allocation failure (tests of the error path): while positive, each
-// device allocation the library would make fails instead, as an exhausted
-// device would make it fail, and the count goes down by one.
-std::atomic<int64_t> opt_fail_alloc{0};
+// Forced allocation failures (tests of the error paths): while positive, each
+// device allocation (or each one of pinned host memory) the library would make
+// fails instead, as an exhausted device would make it fail, and the count goes
+// down by one.
+std::atomic<int64_t> opt_fail_alloc{0}, opt_fail_host_alloc{0};
+
+bool forced_failure(std::atomic<int64_t> &count) {
+    int64_t left = count.load();
+    while (left > 0)
+        if (count.compare_exchange_weak(left, left - 1)) return true;
+    return false;
+}
+
+// (a failure is reported by the call that meets it: it must not stay HIP's last
+// error, which the next kernel launch would report)
+hipError_t allocated(hipError_t e, void **p) {
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        *p = nullptr;
+    }
+    return e;
+}
 
 hipError_t device_alloc(void **p, size_t bytes) {
-    int64_t left = opt_fail_alloc.load();
-    while (left > 0) {
-        if (opt_fail_alloc.compare_exchange_weak(left, left - 1)) {
-            *p = nullptr;
-            return hipErrorOutOfMemory;
-        }
-    }
-    return hipMalloc(p, bytes);
+    return allocated(forced_failure(opt_fail_alloc) ? hipErrorOutOfMemory : hipMalloc(p, bytes), p);
+}
+
+hipError_t host_alloc(void **p, size_t bytes) {
+    return allocated(forced_failure(opt_fail_host_alloc)
+                         ? hipErrorOutOfMemory
+                         : hipHostMalloc(p, bytes, hipHostMallocDefault), p);
 }
 
 std::atomic<int64_t> opt_hist_fpg{0}, opt_hist_chunks{0}, opt_hist_threads{0}, opt_hist_copies{0},
@@ -312,7 +329,7 @@ int host_reserve(Arena &a, size_t bytes) {
     a.host = nullptr;
     a.host_size = 0;
     const size_t want = bytes + bytes / 4 + 4096;
-    HIP_TRY(hipHostMalloc(&a.host, want, hipHostMallocDefault));
+    HIP_TRY(host_alloc(&a.host, want));
     a.host_size = want;
     return FBDT_OK;
 }
@@ -525,14 +542,14 @@ int fbdt_set_option(const char *name, int64_t value) {
         opt_list_copies = value;
     } else if (!strcmp(name, "hist_timeline")) {
         opt_hist_timeline = value != 0;
-    } else if (!strcmp(name, "fail_alloc")) {
+    } else if (!strcmp(name, "fail_alloc") || !strcmp(name, "fail_host_alloc")) {
         // the scratch the library holds is released first, so that the next
-        // call that needs scratch allocates (and fails)
+        // call that needs scratch allocates (and fails); so is the pinned memory
         if (value > 0) {
             const int rc = release_scratch();
             if (rc) return rc;
         }
-        opt_fail_alloc = value;
+        (strcmp(name, "fail_alloc") ? opt_fail_host_alloc : opt_fail_alloc) = value;
     } else if (!strcmp(name, "fit_graphs")) {
         opt_fit_graphs = value;
     } else if (!strcmp(name, "apply_threads")) {

@@ -1003,6 +1003,30 @@ def test_allocation_failure_reports_device_error_and_leaves_the_library_usable()
     assert np.max(np.abs(p.astype(np.float64) - op)) <= 1e-5
 
 
+def test_pinned_memory_failure_reports_device_error_and_leaves_the_library_usable():
+    """Option fail_host_alloc makes the pinned host memory of a fit fail: the
+    fit returns FBDT_E_DEVICE with score_out untouched, and the next one, which
+    needs both kinds of memory again, gives the model of before."""
+    fit_args = (16, 2, 3, 0.1, 0.5, 4)
+    rng = np.random.default_rng(22)
+    codes = fb.Codes.from_numpy(rng.integers(0, 16, (5, 2003)).astype(np.uint8))
+    y = dev(rng.choice(np.array([-1, 1], np.int8), 2003))
+    want = fb.fit(codes, y, *fit_args).export()
+    score = torch.full((2003,), -7.0, dtype=torch.float64, device="cuda")
+    fb.set_option("fail_host_alloc", 1)
+    try:
+        with pytest.raises(fb.FbdtError) as ei:
+            fb.fit(codes, y, *fit_args, score_out=score)
+        assert ei.value.status == "FBDT_E_DEVICE" and "host_alloc" in str(ei.value)
+    finally:
+        fb.set_option("fail_host_alloc", 0)
+    assert bool((score == -7.0).all())
+    got = fb.fit(codes, y, *fit_args, score_out=score).export()
+    for key in ("cut_feature", "cut_bin", "gain", "leaf"):
+        assert np.array_equal(got[key], want[key]), key
+    assert bool((score != -7.0).all())
+
+
 def test_apply_float_nan_without_inner_weights_takes_the_left_branch():
     """In a model without inner weights a NaN value fails every threshold
     test x >= b (section 2.2) and goes left at every node that cuts on it:
