@@ -3030,11 +3030,11 @@ constexpr int kEncodeVecs = 2;
 constexpr int kEncodeTile = kEncodeThreads * kEncodeVecs * 4;
 __global__ __launch_bounds__(kEncodeThreads) void encode_kernel(
     const float *__restrict__ x, int64_t ldx, int64_t n, const float *__restrict__ bounds,
-    int nbins, uint8_t *__restrict__ xb, int64_t ldb, int *__restrict__ err,
-    const int *__restrict__ skip) {
+    int nbins, uint8_t *__restrict__ xb, int64_t ldb, int *err, const int *skip) {
     __shared__ float sb[256];
     const int j = blockIdx.y;
     const int nb = nbins - 1;
+    // (skip and err may be the same word)
     if (skip && (*skip & kErrNan)) return;
     {
         // entry 2^l + p: the boundary that parts the codes p 2^(8 - l) ..
