@@ -3309,19 +3309,24 @@ HistShape plan_histogram(int64_t n, int d, int n_bins, int layer, bool routed, b
     hs.node_groups = (nodes + npg - 1) / npg;
     // Features per workgroup f (one of kHistFpgSizes) and event chunks per
     // XCD c8, from a cost model fitted to 2,000 launches (and their cut scans)
-    // of this kernel on MI355X, by least squares and then by what its choices lose (0.05M-4M events, 12-60
-    // features, 64-256 bins, every layer of depth 4-6, with and without missing
-    // values): a workgroup pays per thousand events (its weights, ids and
-    // routing rows read and decoded: kEvent us by the way the layer is routed)
-    // and per thousand (event, feature) slots (kSlot: the LDS atomics), and for
-    // every LDS row it scans and writes (kRowCost); the launch pays that once per
+    // of this kernel on MI355X, by least squares and then by what its choices
+    // lose (0.05M-4M events, 12-60 features, 64-256 bins, every layer of depth
+    // 4-6, with and without missing values): a workgroup pays per thousand events
+    // (its weights, ids and routing rows read and decoded: per_event us by the way
+    // the layer is routed)
+    // and per thousand (event, feature) slots (slot: the LDS atomics), and for
+    // every LDS row it scans and writes (row_cost); the launch pays that once per
     // round of workgroups, and the chunk partials (written here, summed again
-    // by the cut scan) cost kPartial us per MB.  A layer that routes through
+    // by the cut scan) cost partial us per MB.  A layer that routes through
     // the rows of four parents pays five times a feature's atomics per event,
     // so it takes more features per workgroup than the root.  (With one cost
     // per event for all layers, fitted to 20 and 40 features: 1M x 27, depth 6,
     // layer 3 49.5 us with its cut scan against 28.7; 333k x 27 with missing
-    // values, layers 1-3 20.9, 27.8 and 31.5 us against 17.6, 20.6 and 25.1.)
+    // values, layers 1-3 20.9, 27.8 and 31.5 us against 17.6, 20.6 and 25.1.)  A
+    // histogram by itself pays no routing and no cut scan, but a pass that sums
+    // its chunks one after another: it keeps constants of its own (2.9M x 40, root:
+    // 5 features x 32 chunks 161 us, with the routed layers' constants 8 x 48 and
+    // 172 us; 200k x 27: 1 x 8 100 us, 2 x 16 105).
     const int t_threads = threads > 0 ? threads : 1024;
     const int64_t min_events = (int64_t)kHistE * t_threads;
     const int64_t R = xcd_range(n);
@@ -3331,9 +3336,11 @@ HistShape plan_histogram(int64_t n, int d, int n_bins, int layer, bool routed, b
     if (fpg > 0) {
         f = fpg;
     } else {
-        constexpr double kSlot = 0.042, kPartial = 0.45, kRowCost = 0.13, kMiss = 0.029;
+        const double slot = routed ? 0.042 : 0.057, partial = routed ? 0.45 : 0.25,
+                     row_cost = routed ? 0.13 : 0.0;
+        constexpr double kMiss = 0.029;
         const int parents = layer >= 1 ? 1 << (layer - 1) : 0;
-        double per_event = 0.100;   // ids of the layer itself
+        double per_event = routed ? 0.100 : 0.01;   // ids of the layer itself
         if (routed && parents <= kRoutedMaxParents) {
             per_event = parents == 0 ? 0.089 : parents == 1 ? 0.095 : parents == 2 ? 0.176 : 0.222;
             if (layer >= 1 && !sibling) per_event += kMiss;   // events may stop
@@ -3353,8 +3360,8 @@ HistShape plan_histogram(int64_t n, int d, int n_bins, int layer, bool routed, b
                 const int64_t wgs = kXcds * c8 * g;
                 const double rounds = (double)((wgs + cu_count - 1) / cu_count);
                 const double pmb = (double)(kXcds * c8) * nodes * d * n_bins * 16.0 / 1e6;
-                const double t = rounds * (ek * (per_event + kSlot * cand) + kRowCost * np * cand) +
-                                 kPartial * pmb;
+                const double t = rounds * (ek * (per_event + slot * cand) + row_cost * np * cand) +
+                                 partial * pmb;
                 if (c8_pick == 0 || t < best) {
                     best = t;
                     f = cand;

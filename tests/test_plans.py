@@ -155,3 +155,27 @@ def test_the_swept_cases_sweep(quantile_plan):
         assert q.per > 65_280, (n, d)
         last.append(n - (q.chunks - 1) * q.per)
     assert min(last) <= 65_280
+
+
+class HistShape(C.Structure):
+    _fields_ = [("features_per_group", C.c_int), ("feature_groups", C.c_int),
+                ("nodes_per_group", C.c_int), ("node_groups", C.c_int), ("chunks", C.c_int),
+                ("chunk_events", C.c_int64), ("xcd_events", C.c_int64), ("threads", C.c_int),
+                ("blocks", C.c_int), ("copies", C.c_int), ("copy_stride", C.c_int),
+                ("lds_bytes", C.c_size_t), ("sibling", C.c_bool), ("prefix", C.c_bool)]
+
+
+@pytest.mark.parametrize("n,d,n_bins,layer,shape", [
+    (2_900_000, 40, 256, 0, (5, 32)), (200_000, 27, 200, 0, (1, 8)), (200_000, 27, 200, 1, (1, 8)),
+    (500_000, 20, 256, 0, (2, 24)), (50_000, 100, 256, 4, (2, 8)), (1_000_000, 40, 64, 2, (5, 32)),
+])
+def test_a_histogram_by_itself_takes_few_chunks(n, d, n_bins, layer, shape):
+    """fbdt_histogram's chunks are summed one after another by a pass of its
+    own, so its shapes (features per group, chunks) are not those of a fit's
+    layers; these were the fastest or within 4% of it when timed."""
+    plan = C.CDLL(LIB_PATH)._ZN4fbdt14plan_histogramEliiibbimRKNS_13HistOverridesE
+    plan.restype = HistShape
+    plan.argtypes = [C.c_int64, C.c_int, C.c_int, C.c_int, C.c_bool, C.c_bool, C.c_int,
+                     C.c_size_t, C.c_void_p]
+    s = plan(n, d, n_bins, layer, False, False, CUS, LDS, C.byref((C.c_int * 4)()))
+    assert (s.features_per_group, s.chunks) == shape
