@@ -1439,24 +1439,27 @@ int fbdt_apply_float(const fbdt_model *mc, const float *x, int64_t n, int32_t d,
         fbdt_model::DeviceCopy *copy = nullptr;
         if ((rc = device_copy(m, dev, &copy))) return rc;
         const size_t nb = (size_t)m->n_bins - 1;
-        // cut "bin >= c" of feature j = "x >= boundary c of feature j"
-        // (boundary index c - 1 of its row)
-        auto threshold = [&](size_t k) {
-            return m->boundaries[(size_t)m->cut_feature[k] * nb + m->cut_bin[k] - 1];
-        };
-        // per feature, the ascending distinct thresholds its cuts test (equal
-        // values, +0 and -0 included, decide alike: one entry)
+        // cut "bin >= c" of feature j = "x >= boundary c of feature j" (boundary
+        // index c - 1 of its row).  Per feature, the ascending distinct thresholds
+        // its cuts test (equal values, +0 and -0 included, decide alike: one
+        // entry), and the rank of each bin's among them: the boundaries ascend
+        // with the bin, so the cuts mark bins and nothing is sorted (1,000 trees of
+        // depth 7, first call of a model: 9.6 ms with a sort and a search per node).
         std::vector<std::vector<float>> per;
+        std::vector<uint8_t> rank_of;   // [feature][bin], from 1
         auto collect = [&]() {
             if (!per.empty()) return;
             per.resize(m->n_features);
+            rank_of.assign(per.size() * 256, 0);
             for (size_t k = 0; k < (size_t)T * nin; ++k)
-                per[m->cut_feature[k]].push_back(threshold(k));
-            for (auto &v : per) {
-                std::sort(v.begin(), v.end());
-                v.erase(std::unique(v.begin(), v.end(), [](float a, float b) { return a == b; }),
-                        v.end());
-            }
+                rank_of[(size_t)m->cut_feature[k] * 256 + m->cut_bin[k]] = 1;
+            for (size_t f = 0; f < per.size(); ++f)
+                for (size_t c = 1; c <= nb; ++c)
+                    if (rank_of[f * 256 + c]) {
+                        const float t = m->boundaries[f * nb + c - 1];
+                        if (per[f].empty() || per[f].back() != t) per[f].push_back(t);
+                        rank_of[f * 256 + c] = (uint8_t)per[f].size();
+                    }
         };
         if (!copy->ftab) {
             collect();
@@ -1488,8 +1491,7 @@ int fbdt_apply_float(const fbdt_model *mc, const float *x, int64_t n, int32_t d,
                         "apply_threads)", as.lds_bytes, di.max_lds);
         auto rank = [&](size_t q) {
             collect();
-            const auto &v = per[m->cut_feature[q]];
-            return (uint32_t)(std::lower_bound(v.begin(), v.end(), threshold(q)) - v.begin()) + 1u;
+            return (uint32_t)rank_of[(size_t)m->cut_feature[q] * 256 + m->cut_bin[q]];
         };
         const std::vector<int> strides =
             copy->rec[1].empty()
