@@ -2372,12 +2372,14 @@ __global__ __launch_bounds__(256) void route_kernel(const uint8_t *__restrict__ 
 // to F in tree order.  Leaf values of tpc trees at a time are staged in LDS
 // (all of them when they fit), the codes of a tile of 4 * blockDim events
 // per feature (row stride XS = 4 * blockDim).
-// About 8 vector instructions per event and tree: bound by their issue and
-// by the LDS (7 words of codes and 4 leaf values per four events).  Two events
-// a thread in 16-bit fields (a byte permute and an add per node, 18.5
-// instructions) took 11.9 ms for 50M events of 40 features and 400 trees of
-// depth 3; now 6.6 ms (81%
-// of the vector issue rate, and no bank conflicts).
+// Per four events and tree 33 vector instructions and 11 LDS reads (7 words of
+// codes, 4 leaf values): 8.5 lane instructions per event and tree, issued at 64%
+// of the vector rate at 2.4 GHz, with the LDS reads at about 60% of the LDS's (no
+// bank conflicts) and the waves waiting a third of their time.  The scalar
+// registers that the compiler spills for the two batches lie outside the tree
+// loop.  Two events a thread in 16-bit fields (a byte permute and an add per node,
+// 19 lane instructions) took 11.9 ms for 50M events of 40 features and 400 trees
+// of depth 3; now 6.6 ms.
 constexpr int kApplyBatch = 2;
 
 // Selects, bit by bit, a where m is set and b where it is not.
@@ -2634,7 +2636,7 @@ __global__ __launch_bounds__(1024) void apply_shallow_kernel(
 // order.  With one chain of batches per thread the bulk kernel takes the time
 // of all the trees' loads one after another whatever the number of events
 // (400 trees of depth 3: 78 us a call for 1,000 events of 40 features, here
-// 16 us; 260,000 events: 57 us, about 100 us in the bulk kernel).
+// 13 us; 262,000 events: 59 us, 93 us in the bulk kernel).
 constexpr int kSplitEvents = 256;
 constexpr int kSplitThreads = 1024;
 template <int D, int IN>
@@ -2923,7 +2925,7 @@ __global__ __launch_bounds__(kSplitThreads) void apply_deep_split_kernel(
 // adding one after another, and no add waits for the one before.  The
 // accumulators (8 bytes per event and feature) leave 6 wavefronts per CU for
 // 40 features: bound by the walk's dependent reads at that occupancy.  500,000
-// events of 40 features, 200 trees of depth 3: 232 us (one tree at a time
+// events of 40 features, 200 trees of depth 3: 226 us (one tree at a time
 // with loaded and stored accumulators: 966 us).
 template <int D, bool MISSING>
 __global__ __launch_bounds__(1024) void importance_kernel(
@@ -3905,7 +3907,10 @@ ApplyShape plan_apply(int64_t n, int d_used, int n_trees, int depth, bool missin
     // events of 40 features: 1.58 ms with 8 per CU, 1.33 ms with 12; of 8
     // features: 1.02 ms with 24, 1.07 ms with 32).  A workgroup holds its
     // tile of codes and all trees' weights (and records), or at least 16 KiB
-    // of them at a time.
+    // of them at a time.  Against the other shapes, for ten forests (10 to 3,000
+    // trees of depth 3 to 7, with and without missing values) of 8, 20 and 40
+    // features and 0.5M to 2.9M events: within 10% of the fastest each time, and
+    // within 5% in 90 of 99.
     double best = 0.0;
     int best_t = 0, best_w = 1;
     for (int w = 1; w <= 4; ++w)
