@@ -2547,10 +2547,10 @@ __device__ __forceinline__ void store_scores(const double (&F)[4], int64_t i0, i
 
 constexpr int kInCodes = 0, kInValues = 1, kInValuesFar = 2;
 // IN: what the tile is staged from.  kInValuesFar is for threshold tables that
-// would leave the LDS too little for a tile: its searches read the table
-// through the caches.  With float values the node records
-// carry, instead of the bin c, the rank c' of the node's threshold among its
-// feature's (code >= c' exactly when x >= threshold).
+// would leave the LDS too little for a tile or for the trees: its searches read
+// the table through the caches.  With float values the node records carry,
+// instead of the bin c, the rank c' of the node's threshold among its feature's
+// (code >= c' exactly when x >= threshold).
 template <int D, int IN>
 __global__ __launch_bounds__(1024) void apply_shallow_kernel(
     const uint8_t *__restrict__ xb, int64_t ldb, const float *__restrict__ xf, int64_t ldx,
@@ -2629,8 +2629,9 @@ __global__ __launch_bounds__(1024) void apply_shallow_kernel(
     }
 }
 
-// The same traversal for few events: a workgroup takes kSplitEvents events
-// and its wavefronts share the trees.  Each wavefront finds the leaves that the
+// The same traversal for few events, and for forests so wide that a bulk tile
+// leaves a CU few wavefronts: a workgroup takes kSplitEvents events and its
+// wavefronts share the trees.  Each wavefront finds the leaves that the
 // events reach in its trees (four events per lane, 8 * leaf in the bytes of
 // s_m[tree][lane]); then a thread per event adds the leaf values in tree
 // order.  With one chain of batches per thread the bulk kernel takes the time
@@ -2851,7 +2852,7 @@ __global__ __launch_bounds__(1024) void apply_deep_kernel(
     }
 }
 
-// The deep traversal for few events (see apply_split_kernel).
+// The deep traversal for few events or wide forests (see apply_split_kernel).
 template <bool MISSING, int IN>
 __global__ __launch_bounds__(kSplitThreads) void apply_deep_split_kernel(
     const uint8_t *__restrict__ xb, int64_t ldb, const float *__restrict__ xf, int64_t ldx,
